@@ -461,6 +461,40 @@ static int label_one(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, in
     return run_batch(one, conn, ch, st, local_only, who);
 }
 
+// Workspace of a volume, or false where it is labelled in place, which needs
+// none:
+//  * fewer than 192 bricks of 64 x 16 x 16 (but more than one), or one slice:
+//    the in-place path's bricks are a quarter of that and fill the chip
+//    sooner (100^3, 98 bricks: 55 us in place, 58 here; 129^3, 243 bricks: 67
+//    and 60; 512^3: 730 and 250);
+//  * thin volumes whose workspace would be large (over 150 MB with bricks less
+//    than a third full; at a full 64 x 16 x 16 it is 2.3 bytes per voxel);
+//  * a workspace that cannot be had, and calls on a stream that is being
+//    captured, where nothing may be allocated and the graph may outlive this
+//    stream's workspace.
+static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* ws)
+{
+    const int64_t nb = (int64_t)v.wnbx * v.wnby * v.wnbz;
+    const int64_t n = (int64_t)v.D * v.H * v.W;
+    if (v.D < 2 || (nb > 1 && nb < 192) || (int64_t)v.nbx * v.nby * v.nbz == 1 ||
+        (nb > 4096 && nb * (VOL_WS_W * VOL_WS_H * VOL_WS_D) > 3 * n) ||
+        nb * vol_ws_nodes(conn) > (int64_t)INT32_MAX)
+        return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+    void* base = nullptr;
+    if (get_workspace(vol_workspace(nullptr, nb, conn, nullptr), st, &base) != CCL_OK) {
+        g_err.clear();
+        return false;
+    }
+    vol_workspace(base, nb, conn, ws);
+    return true;
+}
+
 // The built-in tile shape and grids (statistics, ablation, volumes, local step).
 static Choice builtin_choice() { return Choice{&r64::ops, GridChoice{}}; }
 
@@ -700,7 +734,14 @@ int ccl_label_3d(const uint8_t* vol, int32_t D, int32_t H, int32_t W, int64_t pi
     auto magic = [](int64_t d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint64_t)d); };
     v.wmagic = magic(W);
     v.smagic = magic((int64_t)H * W);
-    hipError_t e = r64::launch_volume(v, connectivity, st, active_timer());
+    v.wnbx = (int32_t)(((int64_t)W + VOL_WS_W - 1) / VOL_WS_W);
+    v.wnby = (int32_t)(((int64_t)H + VOL_WS_H - 1) / VOL_WS_H);
+    v.wnbz = (int32_t)(((int64_t)D + VOL_WS_D - 1) / VOL_WS_D);
+    v.wvec = v.vec && W % 4 == 0;
+    VolWs vws;
+    hipError_t e = volume_workspace(v, connectivity, st, &vws)
+                       ? r64::launch_volume_ws(v, vws, connectivity, st, active_timer())
+                       : r64::launch_volume(v, connectivity, st, active_timer());
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     return CCL_OK;
 }

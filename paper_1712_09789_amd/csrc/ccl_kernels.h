@@ -55,8 +55,54 @@ struct VolArgs {
     int32_t nbx, nby, nbz;  // bricks along x, y, z
     int32_t vec;            // labels is 16-byte aligned
     uint32_t wmagic, smagic;  // floor(2^32 / W), floor(2^32 / (H * W)); 0xffffffff for 1
+    int32_t wnbx, wnby, wnbz;  // bricks of the workspace path
+    int32_t wvec;              // every label row is 16-byte aligned
 };
 constexpr int VOL_BRICK_W = 64, VOL_BRICK_H = 8, VOL_BRICK_D = 8;  // voxels per brick (x, y, z)
+
+// Workspace path of volumes: bricks of 64 x 16 x 16 voxels.  Lines of a brick
+// are its rows (6-connectivity) or its bundles of 2 x 2 rows (26).
+constexpr int VOL_WS_W = 64, VOL_WS_H = 16, VOL_WS_D = 16;
+constexpr int vol_ws_lines(int conn) { return VOL_WS_H * VOL_WS_D / (conn == 26 ? 4 : 1); }
+// runs per brick, at most (one per two columns of a line)
+constexpr int vol_ws_runs(int conn) { return vol_ws_lines(conn) * VOL_WS_W / 2; }
+// Components of a brick that touch its faces, at most: each holds a run that
+// does, every run of an outer line or the first or last run of an inner one.
+constexpr int vol_ws_nodes(int conn)
+{
+    const int ly = conn == 26 ? VOL_WS_H / 2 : VOL_WS_H, lz = vol_ws_lines(conn) / ly;
+    const int inner = (ly - 2) * (lz - 2);
+    return (ly * lz - inner) * VOL_WS_W / 2 + 2 * inner;
+}
+// row of the table of first run ids (lines + 1 entries, padded)
+constexpr int vol_ws_base_stride(int conn) { return vol_ws_lines(conn) + 8; }
+
+struct VolWs {
+    uint64_t* bits;    // [bricks][256] foreground of each brick row
+    uint16_t* base;    // [bricks][base stride] id of the first run of each line, then the runs
+    uint16_t* runtab;  // [bricks][runs] per run: its component's number | 0x8000, or the brick
+                       // position of its component's smallest voxel
+    uint64_t* forest;  // [bricks][nodes] (key of parent << 32) | parent node
+    uint32_t* ncomp;   // [bricks] nodes in use
+};
+
+// Carves the workspace of `nb` bricks at `base` into *ws (if any); returns its bytes.
+inline int64_t vol_workspace(void* base, int64_t nb, int conn, VolWs* ws)
+{
+    const int64_t size[5] = {nb * VOL_WS_H * VOL_WS_D * 8, nb * vol_ws_base_stride(conn) * 2,
+                             nb * vol_ws_runs(conn) * 2, nb * vol_ws_nodes(conn) * 8, nb * 4};
+    int64_t at[6] = {0};
+    for (int k = 0; k < 5; ++k) at[k + 1] = at[k] + ((size[k] + 255) & ~int64_t(255));
+    if (ws) {
+        char* p = static_cast<char*>(base);
+        ws->bits = reinterpret_cast<uint64_t*>(p + at[0]);
+        ws->base = reinterpret_cast<uint16_t*>(p + at[1]);
+        ws->runtab = reinterpret_cast<uint16_t*>(p + at[2]);
+        ws->forest = reinterpret_cast<uint64_t*>(p + at[3]);
+        ws->ncomp = reinterpret_cast<uint32_t*>(p + at[4]);
+    }
+    return at[5];
+}
 
 // Images labelled by one set of launches (all of one connectivity).  With n
 // == 1 the image travels in `one` and the tables are unused; otherwise the
@@ -243,6 +289,9 @@ hipError_t launch_ablation(const BatchArgs& b, const Workspace& ws, hipStream_t 
 // Unite components across adjacent slices of a volume (6- or 26-connectivity)
 // and write canonical labels; the slices' labels must already be in place.
 hipError_t launch_volume(const VolArgs& v, int conn, hipStream_t st, KernelTimer* timer);
+// The same labels through a workspace (vol_workspace).
+hipError_t launch_volume_ws(const VolArgs& v, const VolWs& ws, int conn, hipStream_t st,
+                            KernelTimer* timer);
 // Writes *count = 0 (an empty image has no components).
 hipError_t launch_zero_count(int64_t* count, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t st,
