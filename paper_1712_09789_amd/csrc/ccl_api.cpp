@@ -300,12 +300,24 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
     return c;
 }
 
+// Launches of at most this many pixels with a seam between merge groups unite
+// their tiles across every seam in one kernel (k_seam) instead of two levels
+// (k_block, then k_seam between groups): below it the merge is two launches'
+// latency, above it the longer chains of a forest over all tiles cost more
+// than the launch.  640 x 480 and 2048^2 blobs, Bernoulli 0.41 and
+// serpentine at 8-connectivity: 18.4, 24.4 and 19.9 us against 22.7, 31.8 and
+// 22.6; 27.5, 41.0, 34.8 against 31.9, 43.7, 31.7; 3000^2: 39.1, 63.1, 67.6
+// against 42.4, 61.3, 48.1.  Images of one group keep k_block, which is all
+// their merge and leaves their forest flat.
+constexpr int64_t DIRECT_PX = int64_t(1) << 22;
+
 // Sizes of one connectivity class of a batch.
 struct ClassLayout {
     int n = 0;
     int rows = DEFAULT_ROWS;
     std::vector<int64_t> toff, goff, soff;  // prefix offsets (n+1 each)
     int64_t ntiles = 0, ngroups = 0, nseamwg = 0;
+    bool direct = false;  // tiles merged across every seam at once, no groups
     int64_t head = 0;  // bytes of the device tables (0 for a single image)
     int64_t bytes() const { return head + workspace_bytes(ntiles, rows); }
 };
@@ -319,12 +331,18 @@ static int layout_class(std::vector<ImageArgs>& imgs, int conn, const ShapeOps& 
     L.toff.assign(n + 1, 0);
     L.goff.assign(n + 1, 0);
     L.soff.assign(n + 1, 0);
+    int64_t px = 0, seams = 0;
+    for (const ImageArgs& a : imgs) {
+        px += (int64_t)a.H * a.W;
+        seams += ops.image_seam_items(a.ntx, a.nty, a.H, a.W, conn, false);
+    }
+    L.direct = seams > 0 && px <= DIRECT_PX;
     for (int i = 0; i < n; ++i) {
         ImageArgs& a = imgs[i];
         a.tbase = L.toff[i];
         L.toff[i + 1] = L.toff[i] + (int64_t)a.ntx * a.nty;
-        L.goff[i + 1] = L.goff[i] + ops.image_groups(a.ntx, a.nty);
-        const int64_t items = ops.image_seam_items(a.ntx, a.nty, a.H, a.W, conn);
+        L.goff[i + 1] = L.goff[i] + ops.image_groups(a.ntx, a.nty, L.direct);
+        const int64_t items = ops.image_seam_items(a.ntx, a.nty, a.H, a.W, conn, L.direct);
         L.soff[i + 1] = L.soff[i] + (items + SEAM_WG - 1) / SEAM_WG;
     }
     L.ntiles = L.toff[n];
@@ -349,6 +367,7 @@ static int bind_class(const std::vector<ImageArgs>& imgs, const ClassLayout& L, 
     const int n = L.n;
     b = BatchArgs{};
     b.n = n;
+    b.direct = L.direct;
     b.ntiles = L.ntiles;
     b.ngroups = local_only ? 0 : L.ngroups;
     b.nseamwg = local_only ? 0 : L.nseamwg;

@@ -118,6 +118,7 @@ struct BatchArgs {
     int32_t* group_img;  // [ngroups]
     int32_t* seam_img;   // [nseamwg]
     int32_t n;
+    int32_t direct;  // no merge groups: k_seam unites the tiles across every seam
     int64_t ntiles, ngroups, nseamwg;
 };
 
@@ -256,8 +257,10 @@ struct GridChoice {
 // Launchers and tile-grid quantities of one tile-height build.
 struct ShapeOps {
     int rows;
-    int64_t (*image_groups)(int ntx, int nty);  // merge groups of an image
-    int64_t (*image_seam_items)(int ntx, int nty, int H, int W, int conn);  // k_seam work items
+    // merge groups and k_seam work items of an image (direct: no groups,
+    // every seam between tiles is k_seam's)
+    int64_t (*image_groups)(int ntx, int nty, bool direct);
+    int64_t (*image_seam_items)(int ntx, int nty, int H, int W, int conn, bool direct);
     // k_index: fills the image-of-tile/group/seam-workgroup tables of a
     // batch (n > 1); must precede label on the same stream.
     hipError_t (*index)(const BatchArgs& b, hipStream_t st);

@@ -25,7 +25,7 @@
 //            group roots to the forest.
 //   k_seam   (Section 3.2, between groups)  for every foreground pair
 //            straddling a group seam, unite the two group roots in HBM
-//            (atomicMin).
+//            (atomicMin); small launches skip k_block and unite tiles here.
 //   k_final  (Section 3.3)  look up the global root of each border component
 //            and write every label exactly once, from the bitmask and the run
 //            table (no union-find work is repeated).
@@ -260,71 +260,68 @@ __device__ __forceinline__ void st_global16(void* p, int32_t a, int32_t b, int32
 // on the packed word only ever moves a parent to a smaller key.
 // ---------------------------------------------------------------------------
 
-struct Root {
-    uint32_t node;
-    uint32_t key;
-};
-
 __device__ __forceinline__ uint64_t g_ld(const uint64_t* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Reads of the forest during a merge.  A find's first two hops use plain
-// (cacheable) loads: most finds end there, at a root many threads share.  A
-// stale entry still names an ancestor, and a stale "root" is caught by the
-// link's atomic min, which returns the current entry, and the union goes on
-// from there; longer chases switch to coherent loads, which keep chains that
-// are being rewritten from being walked through old entries.
+// Reads of the forest during a merge.  The first hops of a union use plain
+// (cacheable) loads: most unions end within them, at entries many threads
+// share.  A stale entry still names an ancestor, and a stale "root" is caught
+// by the link's atomic min, which returns the current entry, and the union
+// goes on from there; longer walks switch to coherent loads, which keep
+// chains that are being rewritten from being walked through old entries
+// (all loads plain, or coherent from the second hop: within 2 %).
 __device__ __forceinline__ uint64_t g_hop(const uint64_t* p, int step)
 {
-    return step < 2 ? ld_global(p) : g_ld(p);
+    return step < 8 ? ld_global(p) : g_ld(p);
 }
 
-// Root of n, given v = F[n] already loaded.  Halves the path on the way
-// with plain stores: a node is rewritten only after it was read as a
-// non-root (roots are never stored to, and a node that has a parent never
-// becomes a root again), and only with an ancestor, whose key is smaller.
-// Such a store may replace a link another thread made meanwhile with its
-// atomic min; that thread found the node no longer a root (the min returned
-// another parent) and goes on uniting from that parent, so the link it made
-// is not needed.  Atomic mins for the halving made the merge across groups
-// slower where one component crosses the seams many times (all chains pass
-// the same few nodes); plain stores gained on those images (8192^2
-// serpentine 135 -> 111 us) and cost nothing elsewhere.
-__device__ Root g_find_from(uint64_t* F, uint32_t n, uint64_t v)
-{
-    for (int step = 0;; step += 2) {
-        uint32_t p = (uint32_t)v;
-        if (p == n) return Root{n, (uint32_t)(v >> 32)};
-        uint64_t vp = g_hop(F + p, step);
-        uint32_t pp = (uint32_t)vp;
-        if (pp == p) return Root{p, (uint32_t)(vp >> 32)};
-        st_global(F + n, vp);
-        n = pp;
-        v = g_hop(F + n, step + 1);
-    }
-}
-
-// The paper's merge on the HBM forest.  The first loads of both finds are
-// issued together, so a union whose nodes are still roots costs one round
-// trip before the link instead of two.
+// The paper's merge on the HBM forest, without finding both roots: the two
+// paths are climbed together, always on the side whose parent has the larger
+// key, until they meet at one parent (one component already) or that side
+// is a root, which is then linked under the other side's parent (Rem's
+// algorithm with splicing).  Packed entries order parents by key, and every
+// link and every rewritten entry goes to a smaller one, so walks end and the
+// smallest position stays the root.
+// A node left behind by the climb takes the other side's parent, with a plain
+// store: it was read as a non-root (roots are never stored to, and a node
+// that has a parent never becomes a root again), and its old parent goes on
+// to be united with that new one by this very walk.  The store may replace
+// an entry another thread made meanwhile; that thread, too, goes on uniting
+// the parent it read or got back from its atomic min, so no union is lost.
+// Bound by the latency of dependent loads and by device-scope atomics.
+// Finding both roots with path halving took 67 us in k_seam on the 8192^2
+// serpentine of width 3 (16.6 on 8192^2 Bernoulli 0.6, 74 in k_wmerge on 512^3
+// blobs), this walk 17.6 (16.5, 64); halving the climbed path instead of
+// splicing 27 (21, 68).
 __device__ void g_union(uint64_t* F, uint32_t a, uint32_t b)
 {
-    while (true) {
-        const uint64_t va = g_hop(F + a, 0), vb = g_hop(F + b, 0);
-        Root ra = g_find_from(F, a, va);
-        Root rb = g_find_from(F, b, vb);
-        if (ra.node == rb.node) return;
-        if (ra.key < rb.key) { Root t = ra; ra = rb; rb = t; }
-        // ra has the larger key: link it under rb
-        const uint64_t self = ((uint64_t)ra.key << 32) | ra.node;
-        const uint64_t nv = ((uint64_t)rb.key << 32) | rb.node;
-        const uint64_t old = __hip_atomic_fetch_min(F + ra.node, nv, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        if (old == self) return;
-        a = (uint32_t)old;
-        b = rb.node;
+    uint64_t va = g_hop(F + a, 0), vb = g_hop(F + b, 0);
+    for (int step = 1; va != vb; ++step) {
+        if (va < vb) {
+            const uint32_t t = a;
+            a = b;
+            b = t;
+            const uint64_t tv = va;
+            va = vb;
+            vb = tv;
+        }
+        const uint32_t p = (uint32_t)va;
+        if (p == a) {
+            // a root with the larger key: under the other side's parent
+            const uint64_t old = __hip_atomic_fetch_min(F + a, vb, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+            if (old == va) return;
+            // linked meanwhile (or read stale): that parent is still to be united
+            a = (uint32_t)old;
+            va = g_hop(F + a, step);
+        } else {
+            const uint64_t vp = g_hop(F + p, step);
+            st_global(F + a, vb);
+            a = p;
+            va = vp;
+        }
     }
 }
 
@@ -1069,42 +1066,44 @@ __global__ __launch_bounds__(NTB) void k_block(BatchArgs b, Workspace ws)
     }
 }
 
-// Seams between merge groups, united in the HBM forest.  Work items: every
-// position of the horizontal seams on group rows, of the vertical seams on
-// group columns, and (8-connectivity) the two diagonal edges that cross a
-// group column at each seam between tile rows inside a group.
-template <int D>
+// Seams between merge groups of GX x GY tiles, united in the HBM forest: the
+// groups of k_block, or single tiles (1 x 1: every seam, no k_block before).
+// Work items: every position of the horizontal seams on group rows, of the
+// vertical seams on group columns, and (8-connectivity) the two diagonal edges
+// that cross a group column at each seam between tile rows inside a group.
+template <int D, int GX, int GY>
 __global__ __launch_bounds__(SEAM_WG) void k_seam(BatchArgs b, Workspace ws)
 {
     const int img = b.n == 1 ? 0 : ld_uniform(b.seam_img + blockIdx.x);
     const ImageArgs a = batch_image(b, img);
     const int64_t wg = blockIdx.x - (b.n == 1 ? 0 : ld_uniform(b.seam_off + img));
     const int64_t gid = wg * SEAM_WG + threadIdx.x;
-    const int nkh = (a.nty - 1) / BY, nkv = (a.ntx - 1) / BX;
-    const int nbx = (a.ntx + BX - 1) / BX;
+    const int nkh = (a.nty - 1) / GY, nkv = (a.ntx - 1) / GX;
+    const int nbx = (a.ntx + GX - 1) / GX;
     const int64_t nh = (int64_t)nkh * a.W, nv = (int64_t)nkv * a.H;
-    const int64_t nc = D ? (int64_t)(a.nty - 1 - nkh) * (nbx - 1) : 0;
+    const int64_t nc = D && GY > 1 ? (int64_t)(a.nty - 1 - nkh) * (nbx - 1) : 0;
     SeamNodes n;
     int m;
     if (gid < nh) {
-        n = hseam_nodes(a, ws.slots, (int)(gid / a.W + 1) * BY, (int)(gid % a.W));
+        n = hseam_nodes(a, ws.slots, (int)(gid / a.W + 1) * GY, (int)(gid % a.W));
         m = seam_edges<D>(n.ap, n.ac, n.bp, n.bc);
     } else if (gid < nh + nv) {
         const int64_t g = gid - nh;
-        n = vseam_nodes(a, ws.slots, (int)(g / a.H + 1) * BX, (int)(g % a.H));
+        n = vseam_nodes(a, ws.slots, (int)(g / a.H + 1) * GX, (int)(g % a.H));
         m = seam_edges<D>(n.ap, n.ac, n.bp, n.bc);
-    } else if (gid < nh + nv + nc) {
+    } else if (GY > 1 && gid < nh + nv + nc) {
         const int64_t g = gid - nh - nv;
         const int kk = (int)(g / (nbx - 1));
-        const int k = kk + kk / (BY - 1) + 1;  // skip tile rows that start a group
-        const int x = (int)(g % (nbx - 1) + 1) * BPX;
+        const int k = kk + kk / (GY > 1 ? GY - 1 : 1) + 1;  // skip tile rows that start a group
+        const int x = (int)(g % (nbx - 1) + 1) * GX * TW;
         n = hseam_nodes(a, ws.slots, k, x);
         m = seam_edges<D>(n.ap, n.ac, n.bp, n.bc) & (E_PI | E_IP);
     } else {
         m = 0;
         n.ap = n.ac = n.bp = n.bc = -1;
     }
-    // The slots read here name group roots (k_block rewrote them); drop pairs
+    // The slots read here name group roots (k_block rewrote them; tile
+    // representatives for 1 x 1 groups); drop pairs
     // another item of this workgroup already holds: along a seam most
     // foreground stretches join the same two group roots, and one union per
     // distinct pair is enough.  A full table only costs duplicates.
@@ -3218,14 +3217,15 @@ static unsigned tile_grid(int kernel, const BatchArgs& b, unsigned resident, Gri
     return per_tile ? (unsigned)b.ntiles : (unsigned)std::min<int64_t>(b.ntiles, resident);
 }
 
-int64_t image_groups(int ntx, int nty)
+int64_t image_groups(int ntx, int nty, bool direct)
 {
-    if (ntx == 1 && nty == 1) return 0;  // nothing to merge
+    if (direct || (ntx == 1 && nty == 1)) return 0;  // nothing to merge in groups
     return (int64_t)((ntx + BX - 1) / BX) * ((nty + BY - 1) / BY);
 }
 
-int64_t image_seam_items(int ntx, int nty, int H, int W, int conn)
+int64_t image_seam_items(int ntx, int nty, int H, int W, int conn, bool direct)
 {
+    if (direct) return (int64_t)(nty - 1) * W + (int64_t)(ntx - 1) * H;
     const int nbx = (ntx + BX - 1) / BX;
     const int nkh = (nty - 1) / BY, nkv = (ntx - 1) / BX;
     return (int64_t)nkh * W + (int64_t)nkv * H +
@@ -3261,7 +3261,8 @@ static hipError_t launch_all(const BatchArgs& b, const Workspace& ws, hipStream_
     }
     if (b.nseamwg > 0) {
         timer_begin(timer, KIND_SEAM, st);
-        k_seam<D><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
+        if (b.direct) k_seam<D, 1, 1><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
+        else k_seam<D, BX, BY><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
         timer_end(timer, KIND_SEAM, st);
     }
     if (!stats) {
@@ -3351,7 +3352,10 @@ hipError_t launch_ablation(const BatchArgs& b, const Workspace& ws, hipStream_t 
         default: k_local_ablate<0><<<g, NT, 0, st>>>(b, ws, counters); break;
     }
     if (b.ngroups > 0) k_block<0><<<(unsigned)b.ngroups, NTB, 0, st>>>(b, ws);
-    if (b.nseamwg > 0) k_seam<0><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
+    if (b.nseamwg > 0 && b.direct)
+        k_seam<0, 1, 1><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
+    else if (b.nseamwg > 0)
+        k_seam<0, BX, BY><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
     const unsigned fgrid =
         tile_grid(1, b, resident_blocks(k_final<0, false, false>, NT), GridChoice{});
     k_final<0, false, false><<<fgrid, NT, 0, st>>>(b, ws, StatsWs{});
