@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from array import array
 from typing import Sequence
 
 import numpy as np
@@ -340,15 +341,49 @@ def make_descs(imgs: Sequence[torch.Tensor], outs: Sequence[torch.Tensor],
     return arr
 
 
+def _plain_descs(imgs: Sequence[torch.Tensor], outs: Sequence[torch.Tensor], connectivity):
+    """make_descs of images and label buffers that pass every check of
+    _image_args and _out_for, written as five 64-bit words per descriptor; None
+    where anything is out of the ordinary (the checks then run one by one, and
+    raise).  A tensor property costs about 0.1 us to read, so each is read
+    once: field by field, with the checks in functions of their own, the
+    descriptors of 256 images took longer than the GPU takes to label them."""
+    n = len(imgs)
+    if n == 0 or len(outs) != n:
+        return None
+    words = array("q")
+    put, u8, i32 = words.extend, torch.uint8, torch.int32
+    try:
+        per_image = isinstance(connectivity, (list, tuple))
+        conn = 0 if per_image else int(connectivity) & 0xffffffff
+        for i in range(n):
+            im, out = imgs[i], outs[i]
+            size, dev = im.shape, im.get_device()
+            if len(size) != 2 or dev < 0 or im.dtype is not u8 or out.dtype is not i32 \
+                    or out.shape != size or out.get_device() != dev or not out.is_contiguous():
+                return None
+            H, W = size
+            pitch, step = im.stride()
+            if not (0 < H < 1 << 31 and 0 < W < 1 << 31) or step != 1 or pitch < W:
+                return None
+            if per_image:
+                conn = int(connectivity[i]) & 0xffffffff
+            put((im.data_ptr(), H | W << 32, pitch if H > 1 else W, conn, out.data_ptr()))
+    except Exception:
+        return None
+    return (ImageDesc * n).from_buffer(words)
+
+
 def label_batch(imgs: Sequence[torch.Tensor], connectivity=8,
                 outs: Sequence[torch.Tensor] | None = None, stream=None, tile_rows: int = 0):
     """Label several independent images in one call; returns the label
     tensors.  tile_rows as in label()."""
     if outs is None:
         outs = [_out_for(im, None) for im in imgs]
-    else:
+    descs = _plain_descs(imgs, outs, connectivity)
+    if descs is None:
         outs = [_out_for(im, o) for im, o in zip(imgs, outs)]
-    descs = make_descs(imgs, outs, connectivity)
+        descs = make_descs(imgs, outs, connectivity)
     if tile_rows:
         _check(_lib.ccl_label_batch_tiled(descs, len(imgs), int(tile_rows),
                                           _stream_handle(stream)))

@@ -194,20 +194,28 @@ static KernelTimer* active_timer() { return g_timing_mask ? &g_timer : nullptr; 
 // ---------------------------------------------------------------------------
 
 static int validate(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, int32_t conn,
-                    const int32_t* labels, const char* who)
+                    const int32_t* labels, const char* who, int32_t index = -1)
 {
-    if (H < 0 || W < 0) return fail(CCL_ERR_INVALID_ARG, "%s: negative size %dx%d", who, H, W);
+    // the caller and, in a batch, the image: formatted only for a message
+    auto at = [&] {
+        return index < 0 ? std::string(who)
+                         : std::string(who) + "[" + std::to_string(index) + "]";
+    };
+    if (H < 0 || W < 0)
+        return fail(CCL_ERR_INVALID_ARG, "%s: negative size %dx%d", at().c_str(), H, W);
     if (conn != 4 && conn != 8)
-        return fail(CCL_ERR_INVALID_ARG, "%s: connectivity %d is not 4 or 8", who, conn);
+        return fail(CCL_ERR_INVALID_ARG, "%s: connectivity %d is not 4 or 8", at().c_str(), conn);
     if (H == 0 || W == 0) return CCL_OK;
     if ((int64_t)H * (int64_t)W > (int64_t)INT32_MAX)
-        return fail(CCL_ERR_TOO_LARGE, "%s: %dx%d pixels exceed int32 labels", who, H, W);
-    if (!img || !labels) return fail(CCL_ERR_INVALID_ARG, "%s: null pointer", who);
+        return fail(CCL_ERR_TOO_LARGE, "%s: %dx%d pixels exceed int32 labels", at().c_str(), H, W);
+    if (!img || !labels) return fail(CCL_ERR_INVALID_ARG, "%s: null pointer", at().c_str());
     if (pitch < W)
-        return fail(CCL_ERR_INVALID_ARG, "%s: pitch %lld < width %d", who, (long long)pitch, W);
+        return fail(CCL_ERR_INVALID_ARG, "%s: pitch %lld < width %d", at().c_str(),
+                    (long long)pitch, W);
     const uintptr_t i0 = (uintptr_t)img, i1 = i0 + (uintptr_t)((int64_t)(H - 1) * pitch + W);
     const uintptr_t l0 = (uintptr_t)labels, l1 = l0 + (uintptr_t)((int64_t)H * W * 4);
-    if (i0 < l1 && l0 < i1) return fail(CCL_ERR_INVALID_ARG, "%s: img and labels overlap", who);
+    if (i0 < l1 && l0 < i1)
+        return fail(CCL_ERR_INVALID_ARG, "%s: img and labels overlap", at().c_str());
     return CCL_OK;
 }
 
@@ -567,9 +575,7 @@ static int label_batch(const ccl_image_desc* descs, int32_t n, int forced_rows, 
     int64_t class_px[2] = {0, 0}, class_n[2] = {0, 0};
     for (int32_t i = 0; i < n; ++i) {
         const ccl_image_desc& d = descs[i];
-        char w[64];
-        snprintf(w, sizeof w, "%s[%d]", who, i);
-        int rc = validate(d.img, d.H, d.W, d.pitch_bytes, d.connectivity, d.labels, w);
+        int rc = validate(d.img, d.H, d.W, d.pitch_bytes, d.connectivity, d.labels, who, i);
         if (rc != CCL_OK) return rc;
         if (d.H == 0 || d.W == 0) continue;
         class_px[d.connectivity == 8] += (int64_t)d.H * d.W;
@@ -816,9 +822,8 @@ int ccl_plan_create(const ccl_image_desc* descs, int32_t n, void* stream, ccl_pl
     int64_t class_px[2] = {0, 0}, class_n[2] = {0, 0};
     for (int32_t i = 0; i < n; ++i) {
         const ccl_image_desc& d = descs[i];
-        char who[64];
-        snprintf(who, sizeof who, "ccl_plan_create[%d]", i);
-        int rc = validate(d.img, d.H, d.W, d.pitch_bytes, d.connectivity, d.labels, who);
+        int rc = validate(d.img, d.H, d.W, d.pitch_bytes, d.connectivity, d.labels,
+                          "ccl_plan_create", i);
         if (rc != CCL_OK) return rc;
         if (d.H == 0 || d.W == 0) continue;
         class_px[d.connectivity == 8] += (int64_t)d.H * d.W;
