@@ -242,8 +242,7 @@ static ImageArgs make_args(const uint8_t* img, int32_t H, int32_t W, int64_t pit
     a.W = W;
     a.ntx = (int32_t)(((int64_t)W + TW - 1) / TW);
     a.nty = (int32_t)(((int64_t)H + rows - 1) / rows);
-    a.unused = 0;
-    a.vec_out = ((uintptr_t)labels % 16 == 0) && (W % 4 == 0);
+    a.unused[0] = a.unused[1] = 0;
     a.wmagic = W == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint64_t)W);
     a.lbase = 0;
     a.tbase = 0;
@@ -762,7 +761,6 @@ int ccl_label_3d(const uint8_t* vol, int32_t D, int32_t H, int32_t W, int64_t pi
     v.wnbx = (int32_t)(((int64_t)W + VOL_WS_W - 1) / VOL_WS_W);
     v.wnby = (int32_t)(((int64_t)H + VOL_WS_H - 1) / VOL_WS_H);
     v.wnbz = (int32_t)(((int64_t)D + VOL_WS_D - 1) / VOL_WS_D);
-    v.wvec = v.vec && W % 4 == 0;
     VolWs vws;
     hipError_t e = volume_workspace(v, connectivity, st, &vws)
                        ? r64::launch_volume_ws(v, vws, connectivity, st, active_timer())

@@ -37,8 +37,7 @@ struct ImageArgs {
     int32_t ntx, nty;  // tile grid
     uint32_t wmagic;   // floor(2^32 / W) (0xffffffff for W = 1), for division by W
     int32_t lbase;     // added to every label written (a slice's first voxel position)
-    int32_t unused;    // keeps the layout at 64 bytes
-    int32_t vec_out;   // labels rows are 16-byte aligned (W % 4 == 0)
+    int32_t unused[2];  // keeps the layout at 64 bytes
     int64_t tbase;     // global index of the image's first tile in the workspace
 };
 // 64 bytes: the kernels read an image's entry with one scalar load.
@@ -56,7 +55,6 @@ struct VolArgs {
     int32_t vec;            // labels is 16-byte aligned
     uint32_t wmagic, smagic;  // floor(2^32 / W), floor(2^32 / (H * W)); 0xffffffff for 1
     int32_t wnbx, wnby, wnbz;  // bricks of the workspace path
-    int32_t wvec;              // every label row is 16-byte aligned
 };
 constexpr int VOL_BRICK_W = 64, VOL_BRICK_H = 8, VOL_BRICK_D = 8;  // voxels per brick (x, y, z)
 

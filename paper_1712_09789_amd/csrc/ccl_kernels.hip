@@ -253,6 +253,33 @@ __device__ __forceinline__ void st_global16(void* p, int32_t a, int32_t b, int32
     st_global(reinterpret_cast<v4u32*>(p), v);
 }
 
+// The same at any multiple of four bytes: label rows of odd widths start
+// anywhere, and a store that straddles two cache lines costs less than four
+// stores (256 images of random widths: k_final 121 us with dword stores of
+// sixteen consecutive labels, 117 with these; 201 x 301 x 333 volume: k_wfinal
+// 35 with a row per wavefront store, 28).
+typedef uint32_t v4u32u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void st_labels4(int32_t* p, int32_t a, int32_t b, int32_t c, int32_t d)
+{
+    v4u32u v;
+    v.x = (uint32_t)a;
+    v.y = (uint32_t)b;
+    v.z = (uint32_t)c;
+    v.w = (uint32_t)d;
+    st_global(reinterpret_cast<v4u32u*>(p), v);
+}
+// The first n of them (n may be negative): the end of a row cut by the edge.
+__device__ __forceinline__ void st_labels(int32_t* p, const int32_t* o, int n)
+{
+    if (n >= 4) {
+        st_labels4(p, o[0], o[1], o[2], o[3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k < n) st_global(p + k, o[k]);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // HBM forest over border components.  Entry = (key of parent << 32) | parent
 // node; a root stores its own key and id.  Keys (raster position of a tile
@@ -487,8 +514,7 @@ __device__ __forceinline__ ImageArgs batch_image(const BatchArgs& b, int i)
     r.nty = p->nty;
     r.wmagic = p->wmagic;
     r.lbase = p->lbase;
-    r.unused = 0;
-    r.vec_out = p->vec_out;
+    r.unused[0] = r.unused[1] = 0;
     r.tbase = p->tbase;
     return r;
 }
@@ -1258,47 +1284,26 @@ __device__ void final_tile(const BatchArgs& b, const Workspace& ws, const StatsW
         }
     }
 
-    // write the labels: 16 threads per tile row, 4 pixels per thread
+    // write the labels: 16 threads per tile row, four consecutive pixels and
+    // one store per thread, at whatever alignment the row has
     const int xmax = a.W - gx0;  // pixels of this tile inside the image
-    if (a.vec_out && xmax >= TW) {
-        // whole aligned rows: four consecutive pixels per thread, one
-        // 16-byte store
-        for (int c = tid; c < TILE_ROWS * 16; c += NT) {
-            const int r = c >> 4, x0 = (c & 15) * 4;
-            const int gy = gy0 + r;
-            if (gy >= a.H) continue;
-            const int l = D ? r >> 1 : r;
-            const uint64_t ls = sh.LS[l];
-            const uint32_t m4 = (uint32_t)(sh.M[r] >> x0) & 15u;
-            const uint32_t s4 = (uint32_t)(ls >> x0) & 15u;
-            uint32_t cnt = sh.base[l] + popc64(ls & ~(~0ull << x0));  // runs starting left of x0
-            int32_t o[4];
+    for (int c = tid; c < TILE_ROWS * 16; c += NT) {
+        const int r = c >> 4, x0 = (c & 15) * 4;
+        const int gy = gy0 + r;
+        if (gy >= a.H) continue;
+        const int l = D ? r >> 1 : r;
+        const uint64_t ls = sh.LS[l];
+        const uint32_t m4 = (uint32_t)(sh.M[r] >> x0) & 15u;
+        const uint32_t s4 = (uint32_t)(ls >> x0) & 15u;
+        uint32_t cnt = sh.base[l] + popc64(ls & ~(~0ull << x0));  // runs starting left of x0
+        int32_t o[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                cnt += (s4 >> k) & 1u;
-                // a foreground pixel has its run start at or left of it, so cnt >= 1
-                o[k] = ((m4 >> k) & 1u) ? sh.lab[cnt ? cnt - 1 : 0] : 0;
-            }
-            st_global16(a.labels + (int64_t)gy * a.W + gx0 + x0, o[0], o[1], o[2], o[3]);
+        for (int k = 0; k < 4; ++k) {
+            cnt += (s4 >> k) & 1u;
+            // a foreground pixel has its run start at or left of it, so cnt >= 1
+            o[k] = ((m4 >> k) & 1u) ? sh.lab[cnt ? cnt - 1 : 0] : 0;
         }
-    } else {
-        // rows not 16-byte aligned, or cut by the image edge: pixels
-        // x, x + 16, x + 32, x + 48 per thread, so that each store
-        // instruction writes sixteen consecutive labels of a row
-        for (int c = tid; c < TILE_ROWS * 16; c += NT) {
-            const int r = c >> 4, x = c & 15;
-            const int gy = gy0 + r;
-            if (gy >= a.H) continue;
-            const int l = D ? r >> 1 : r;
-            const uint64_t m = sh.M[r];
-            int32_t* row = a.labels + (int64_t)gy * a.W + gx0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int xk = x + 16 * k;
-                if (xk < xmax)
-                    st_global(row + xk, ((m >> xk) & 1ull) ? sh.lab[run_id<D>(sh, l, xk)] : 0);
-            }
-        }
+        st_labels(a.labels + (int64_t)gy * a.W + gx0 + x0, o, xmax - x0);
     }
 }
 
@@ -2516,8 +2521,8 @@ __global__ __launch_bounds__(VNT) void k_vfinal(VolArgs v)
 // byte of bits and row bases plus two bytes per run each way, where the
 // in-place path above writes, reads and rewrites the whole label map.  512^3
 // blobs at 26-connectivity: 748 us in place (local 271, merge 268, relabel
-// 196), 248 here (78, 74, 96; the bytes alone take 118 at the copy rate);
-// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 137 (72, 29, 34).
+// 196), 239 here (78, 64, 96; the bytes alone take 118 at the copy rate);
+// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 128 (73, 26, 28).
 // The local step is bound by instruction issue (63 of its 78 us), the merge
 // by device-scope atomics on the forest and the loads that lead to them, the
 // relabel by its stores (5.6 TB/s).
@@ -3111,39 +3116,22 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wfinal(VolArgs v, VolWs ws)
         }
     }
     __syncthreads();
-    const int xmax = v.W - bk.x0;
-    if (v.wvec && xmax >= WB_W) {
-        // whole aligned rows: four labels per lane, four rows per wavefront store
-        const int x0 = (tid & 15) * 4;
-        for (int r = tid >> 4; r < WB_ROWS; r += G::NT / 16) {
-            const int y = bk.y0 + r % WB_H, z = bk.z0 + r / WB_H;
-            if (y >= v.H || z >= v.D) continue;
-            const int l = C == 26 ? (r / (2 * WB_H)) * G::LH + (r % WB_H) / 2 : r;
-            const uint64_t lm = line_mask(sh, l), ls = lm & ~(lm << 1);
-            const uint32_t m4 = (uint32_t)(sh.M[r] >> x0) & 15u, s4 = (uint32_t)(ls >> x0) & 15u;
-            uint32_t cnt = sh.base[l] + popc64(ls & ~(~0ull << x0));
-            int32_t o[4];
+    // four labels per lane, four rows per wavefront store
+    const int xmax = v.W - bk.x0, x0 = (tid & 15) * 4;
+    for (int r = tid >> 4; r < WB_ROWS; r += G::NT / 16) {
+        const int y = bk.y0 + r % WB_H, z = bk.z0 + r / WB_H;
+        if (y >= v.H || z >= v.D) continue;
+        const int l = C == 26 ? (r / (2 * WB_H)) * G::LH + (r % WB_H) / 2 : r;
+        const uint64_t lm = line_mask(sh, l), ls = lm & ~(lm << 1);
+        const uint32_t m4 = (uint32_t)(sh.M[r] >> x0) & 15u, s4 = (uint32_t)(ls >> x0) & 15u;
+        uint32_t cnt = sh.base[l] + popc64(ls & ~(~0ull << x0));
+        int32_t o[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                cnt += (s4 >> k) & 1u;
-                o[k] = ((m4 >> k) & 1u) ? sh.lab[cnt ? cnt - 1u : 0u] : 0;
-            }
-            st_global16(v.labels + (int64_t)z * S + (int64_t)y * v.W + bk.x0 + x0, o[0], o[1],
-                        o[2], o[3]);
+        for (int k = 0; k < 4; ++k) {
+            cnt += (s4 >> k) & 1u;
+            o[k] = ((m4 >> k) & 1u) ? sh.lab[cnt ? cnt - 1u : 0u] : 0;
         }
-    } else {
-        // rows off 16-byte alignment or cut by the volume's edge: a row per
-        // wavefront store, one label per lane
-        const int lane = tid & 63;
-        for (int r = tid >> 6; r < WB_ROWS; r += G::NT / 64) {
-            const int y = bk.y0 + r % WB_H, z = bk.z0 + r / WB_H;
-            if (y >= v.H || z >= v.D) continue;
-            const int l = C == 26 ? (r / (2 * WB_H)) * G::LH + (r % WB_H) / 2 : r;
-            const uint64_t lm = line_mask(sh, l), ls = lm & ~(lm << 1);
-            const bool fg = (sh.M[r] >> lane) & 1ull;
-            const int32_t o = fg ? sh.lab[sh.base[l] + popc64(ls & upto(lane)) - 1u] : 0;
-            if (lane < xmax) st_global(v.labels + (int64_t)z * S + (int64_t)y * v.W + bk.x0 + lane, o);
-        }
+        st_labels(v.labels + (int64_t)z * S + (int64_t)y * v.W + bk.x0 + x0, o, xmax - x0);
     }
 }
 
