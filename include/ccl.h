@@ -243,12 +243,10 @@ int ccl_label_local(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
 /*
  * Launch policy, for callers that tune it (paper_1712_09789_amd/tune.py
  * does): per launch class, pixel bucket and connectivity, the tile height
- * (the paper's block shape, Section 4.1) and the grid of the two per-tile
- * kernels (the local step and the final relabel).  Each of those runs either
- * as a persistent grid (one workgroup per resident slot, the next tile's
- * loads in flight while the current one is labelled) or with one workgroup
- * per tile (the dispatcher balances tiles of unequal cost).  Labels never
- * depend on any of these choices.
+ * (the paper's block shape, Section 4.1) and the grid of the final relabel,
+ * which runs either as a persistent grid (one workgroup per resident slot,
+ * the next tile's loads in flight while the current one is labelled) or with
+ * one workgroup per tile.  Labels never depend on any of these choices.
  *   batch         0 = calls with one image (ccl_label, plans of one image),
  *                 1 = calls with several (ccl_label_batch, plans); chosen by
  *                 the number of non-empty images of one connectivity
@@ -257,9 +255,10 @@ int ccl_label_local(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  *                 bucket's bound and above the previous one
  *   connectivity  4 or 8
  *   tile_rows     0 = built-in (64), or 32, 64, 128
- *   local, final_ -1 = the built-in choice (local step per tile beyond four
- *                 times the resident workgroups, final relabel persistent),
- *                 0 = persistent, 1 = one workgroup per tile
+ *   local         -1, 0 or 1; no effect (the local step runs one workgroup
+ *                 per tile; kept for callers and saved policies that set it)
+ *   final_        -1 = the built-in choice (persistent), 0 = persistent, 1 =
+ *                 one workgroup per tile
  * ccl_label_stats, ccl_label_3d, ccl_label_ablation and ccl_label_local
  * always use the built-in tile height and grids.  Process-wide; applies to
  * launches enqueued (and plans created) afterwards.  CCL_OK, or

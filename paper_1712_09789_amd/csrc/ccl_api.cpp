@@ -256,9 +256,9 @@ static int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
 // ---------------------------------------------------------------------------
 //
 // A policy entry per (launch class: one image / several, pixel bucket,
-// connectivity) fixes the tile height and the launch grids of k_local and
-// k_final; zero / -1 entries keep the built-in choices (64-row tiles, the
-// kernels' own grid rule).  A tuner (tune.py) measures and sets them.
+// connectivity) fixes the tile height and the launch grid of k_final; zero /
+// -1 entries keep the built-in choices (64-row tiles, the kernel's own grid
+// rule).  A tuner (tune.py) measures and sets them.
 
 static const ShapeOps* const kShapes[NSHAPES] = {&r32::ops, &r64::ops, &r128::ops};
 constexpr int POLICY_BUCKETS = 5;
@@ -267,7 +267,7 @@ static const int64_t kBucketPx[POLICY_BUCKETS] = {int64_t(1) << 22, int64_t(1) <
 
 struct PolicyEntry {
     std::atomic<int> rows{0};  // 0 = built-in (DEFAULT_ROWS)
-    std::atomic<int> local{-1}, final_{-1};
+    std::atomic<int> final_{-1};
 };
 static PolicyEntry g_policy[2][POLICY_BUCKETS][2];  // [batch][bucket][connectivity == 8]
 
@@ -302,7 +302,6 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
     const PolicyEntry& e = g_policy[batch][policy_bucket(px)][conn == 8];
     const int rows = e.rows.load(std::memory_order_relaxed);
     c.ops = shape_for_rows(rows ? rows : DEFAULT_ROWS);
-    c.grid.local = e.local.load(std::memory_order_relaxed);
     c.grid.final_ = e.final_.load(std::memory_order_relaxed);
     return c;
 }
@@ -922,7 +921,6 @@ int ccl_set_launch_policy(int32_t batch, int32_t bucket, int32_t connectivity,
                     batch, bucket, POLICY_BUCKETS - 1, connectivity, tile_rows, local, final_);
     PolicyEntry& e = g_policy[batch][bucket][connectivity == 8];
     e.rows.store(tile_rows, std::memory_order_relaxed);
-    e.local.store(local, std::memory_order_relaxed);
     e.final_.store(final_, std::memory_order_relaxed);
     return CCL_OK;
 }

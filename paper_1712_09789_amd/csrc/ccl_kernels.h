@@ -245,10 +245,9 @@ void timer_end(KernelTimer* t, int kind, hipStream_t st);
 
 constexpr int SEAM_WG = 256;  // k_seam workgroup size
 
-// Launch grid of k_local and k_final: -1 = built-in rule, 0 = persistent (one
-// workgroup per resident slot), 1 = one workgroup per tile.
+// Launch grid of k_final: -1 = built-in rule, 0 = persistent (one workgroup per
+// resident slot), 1 = one workgroup per tile.
 struct GridChoice {
-    int local = -1;
     int final_ = -1;
 };
 

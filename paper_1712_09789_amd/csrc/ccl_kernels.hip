@@ -2,8 +2,7 @@
 //
 // The image is cut into tiles of 64 x TILE_ROWS pixels: one 64-bit
 // foreground mask per tile row, so the paper's row scan becomes bit
-// arithmetic on a word.  A workgroup of 4 * TILE_ROWS threads owns a tile
-// (one sixteen-pixel chunk of a row each).  The file is compiled once per
+// arithmetic on a word.  A workgroup owns a tile.  The file is compiled once per
 // tile height (32, 64 and 128 rows: the paper's block shape is its tuning
 // knob), and the host picks the height per call.
 //
@@ -80,9 +79,6 @@ struct Geo {
     static constexpr int TPL = NT / NL;                       // threads per line
     static constexpr int WIN = TW / TPL;                      // columns per thread
     static constexpr int MAXR = NL * (TW / 2);                // runs per tile, at most
-    // refinement edges per tile, at most: one per column and line boundary
-    // (8-connectivity), one per stretch start of T & B (4-connectivity)
-    static constexpr int MAXE = NL * (D ? TW : TW / 2);
 };
 static_assert(Geo<0>::MAXR <= RUNTAB_PER_TILE && Geo<1>::MAXR <= RUNTAB_PER_TILE, "run table");
 // packed LDS parents hold a 16-bit tile key and a 16-bit run id
@@ -412,27 +408,6 @@ __device__ __forceinline__ uint32_t run_id(const Lines<D>& sh, int l, int x)
     return sh.base[l] + popc64(sh.LS[l] & upto(x)) - 1u;
 }
 
-// Row of line l that faces the line above / below it.
-template <int D>
-__device__ __forceinline__ uint64_t top_row(const Lines<D>& sh, int l)
-{
-    return D ? sh.M[2 * l] : sh.M[l];
-}
-template <int D>
-__device__ __forceinline__ uint64_t bottom_row(const Lines<D>& sh, int l)
-{
-    return D ? sh.M[2 * l + 1] : sh.M[l];
-}
-
-// Tile position (y * 64 + x) of the smallest pixel of run [a, e] of line l.
-template <int D>
-__device__ __forceinline__ uint32_t run_key(const Lines<D>& sh, int l, int a, int e)
-{
-    if (!D) return (uint32_t)(l * TW + a);
-    const uint64_t top = sh.M[2 * l] & span_mask(a, e);
-    return top ? (uint32_t)(2 * l * TW + ctz64(top)) : (uint32_t)((2 * l + 1) * TW + a);
-}
-
 // Run list: RL[id] = start column | line << 6, for every run of the tile.
 // Thread tid takes one window of Geo<D>::WIN columns of one line.  Needs
 // build_lines; the caller synchronises before RL is read.
@@ -448,16 +423,30 @@ __device__ __forceinline__ void list_runs(const Lines<D>& sh, uint16_t* RL, int 
         RL[id] = (uint16_t)((__builtin_ctz(r) + wlo) | (wl << 6));
 }
 
-template <int D>
-struct LocalShared : Lines<D> {
-    uint32_t P[Geo<D>::MAXR];    // parent of each run, packed (key << 16) | id
-    uint32_t nedges;             // refinement edges listed so far
-    union {
-        uint32_t EL[Geo<D>::MAXE];     // refinement edge: lower run | upper run << 16
-        uint16_t h[TILE_ROWS * 4];     // 16-pixel masks as produced by the byte load
-        uint64_t w[TILE_ROWS];         // the same bits as one word per row
-    } u;
+// Work split of the local step: WPL threads per line, a window of columns each.
+template <int D, int WPL>
+struct LGeo : Geo<D> {
+    static constexpr int NTL = Geo<D>::NL * WPL;             // threads per tile
+    static constexpr int WIN = TW / WPL;                     // columns per thread
+    static constexpr int CPT = TILE_ROWS * 4 / NTL;          // sixteen-pixel chunks per thread
+    static constexpr int SPL = (NSLOTS + NTL - 1) / NTL;     // border slots per thread, at most
+    static_assert(WIN <= 32 && CPT >= 1 && CPT * NTL == TILE_ROWS * 4, "windows and chunks");
 };
+template <int D>
+struct LocalShared {
+    uint64_t M[TILE_ROWS];              // foreground mask of each tile row
+    uint64_t LM[D ? Geo<D>::NL : 1];    // 8-connectivity: foreground columns of each strip
+    uint32_t base[Geo<D>::NL + 1];      // id of the first run of each line; base[NL] = runs
+    // parent of each run, packed (key << 16) | id; behind the tile's runs, its
+    // refinement edges (lower run | upper run << 16)
+    uint32_t P[Geo<D>::MAXR];
+    uint32_t nedges;                    // refinement edges found so far
+};
+template <int D>
+__device__ __forceinline__ uint64_t line_of(const LocalShared<D>& sh, int l)
+{
+    return D ? sh.LM[l] : sh.M[l];
+}
 
 // Border slot s -> tile-local (x, y).  Slots: top row, bottom row, left
 // column, right column.
@@ -606,55 +595,99 @@ __device__ __forceinline__ uint32_t chunk_mask(const Chunk& k)
     return (m >> k.off) & ((1u << k.n) - 1u);
 }
 
-// The local step on tile t; sh.u.h holds its foreground bits on entry.
-template <int D>
+// The local step on tile t; sh.M holds its foreground bits on entry (visible
+// to all threads).
+// Bound by instruction issue on images with work in most tiles (8192^2
+// Bernoulli 0.6, 4-connected: 98 of 121 us with four threads per line, a
+// prefetching persistent loop and a list of its own for the edges), so with
+// many tiles it runs with half the threads per line, one tile per workgroup
+// and the edges behind the runs in P (9 and 5 KB of LDS keep 32 wavefronts per
+// compute unit): 121 -> 97 us there, 37 -> 30 on 4096^2 Bernoulli 0.5
+// (8-connected), 122 -> 82 on 256 mixed images, 48 -> 31 on 32 frames, 47 -> 34
+// on the 8192^2 serpentine.  One thread fewer per line again (8-connected) was
+// slower on noise (31.4), four threads per line at 4-connectivity too (112).
+template <int D, int WPL>
 __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<D>& sh, int t,
                            int tid)
 {
-    using G = Geo<D>;
+    using G = LGeo<D, WPL>;
+    constexpr int NTL = G::NTL;
     const int tx = t % a.ntx, ty = t / a.ntx;
     const int gx0 = tx * TW, gy0 = ty * TILE_ROWS;
 
     const int64_t T = a.tbase + t;  // global tile index (workspace)
-    if (tid < TILE_ROWS) {
-        const uint64_t m = sh.u.w[tid];
-        sh.M[tid] = m;
-        ws.bits[T * TILE_ROWS + tid] = m;
+    for (int r = tid; r < TILE_ROWS; r += NTL) ws.bits[T * TILE_ROWS + r] = sh.M[r];
+    if (tid < 64) {
+        // line masks, and dense run-id bases: a scan across the first wavefront
+        constexpr int LPL = (G::NL + 63) / 64;  // consecutive lines per lane
+        uint32_t cnt[LPL], tot = 0;
+#pragma unroll
+        for (int k = 0; k < LPL; ++k) {
+            const int l = tid * LPL + k;
+            cnt[k] = 0;
+            if (l < G::NL) {
+                const uint64_t lm = D ? (sh.M[2 * l] | sh.M[2 * l + 1]) : sh.M[l];
+                if (D) sh.LM[l] = lm;
+                cnt[k] = popc64(lm & ~(lm << 1));
+            }
+            tot += cnt[k];
+        }
+        uint32_t inc = tot;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(inc, off, 64);
+            if (tid >= off) inc += o;
+        }
+        uint32_t run = inc - tot;
+#pragma unroll
+        for (int k = 0; k < LPL; ++k) {
+            const int l = tid * LPL + k;
+            if (l < G::NL) sh.base[l] = run;
+            run += cnt[k];
+        }
+        if (tid == 63) {
+            sh.base[G::NL] = inc;
+            sh.nedges = 0u;
+        }
     }
     __syncthreads();
-    build_lines<D>(sh, tid);
 
     // Two passes walk the bits of a column window (the runs that start in it,
     // and its edges to the line above); the union-find passes walk dense run
-    // ids (thread tid takes ids tid, tid + NT, ...) so that every lane has
+    // ids (thread tid takes ids tid, tid + NTL, ...) so that every lane has
     // work.
     const uint32_t R = sh.base[G::NL];
     if (tid == 0) ws.nruns[T] = R;
-    const int wl = tid / G::TPL;              // this thread's line
-    const int wlo = (tid % G::TPL) * G::WIN;  // and first column of its window
-    constexpr uint32_t WMASK = (1u << G::WIN) - 1u;
+    const int l = tid / WPL;                // this thread's line
+    const int wlo = (tid % WPL) * G::WIN;   // and first column of its window
+    constexpr uint32_t WMASK = (uint32_t)((1ull << G::WIN) - 1ull);
+    const uint64_t left = ~(~0ull << wlo);
+    const uint64_t lm = line_of(sh, l), lsl = lm & ~(lm << 1);
+    const uint32_t lslw = (uint32_t)(lsl >> wlo) & WMASK;  // runs starting in the window
+    // runs of the line starting left of the window, less one: plus the starts
+    // at or left of a column of the window = the run at that column
+    const uint32_t prel = sh.base[l] + popc64(lsl & left) - 1u;
     // Row connection (Section 3.1.2): every run is one provisional label,
     // keyed by its smallest pixel (the paper's provisional label =
     // position).  Each thread takes the runs that start in its window.
     {
-        const uint64_t ls = sh.LS[wl], lm = sh.LM[wl];
-        uint32_t id = sh.base[wl] + popc64(ls & ~(~0ull << wlo));
-        for (uint32_t r = (uint32_t)(ls >> wlo) & WMASK; r; r &= r - 1u, ++id) {
+        uint32_t id = prel + 1u;
+        const uint64_t top = D ? sh.M[2 * l] : 0ull;
+        for (uint32_t r = lslw; r; r &= r - 1u, ++id) {
             const int s0 = __builtin_ctz(r) + wlo;
             uint32_t key;
             if (!D) {
-                key = (uint32_t)(wl * TW + s0);
+                key = (uint32_t)(l * TW + s0);
             } else {
                 // first top-row pixel of the strip run, else its bottom-row start
                 const int len = ctz64_or64(~(lm >> s0));
-                const int tf = ctz64_or64(sh.M[2 * wl] >> s0);
-                key = tf < len ? (uint32_t)(2 * wl * TW + s0 + tf)
-                               : (uint32_t)((2 * wl + 1) * TW + s0);
+                const int tf = ctz64_or64(top >> s0);
+                key = tf < len ? (uint32_t)(2 * l * TW + s0 + tf)
+                               : (uint32_t)((2 * l + 1) * TW + s0);
             }
             sh.P[id] = pk(key, id);
         }
     }
-    if (tid == 0) sh.nedges = 0u;
     __syncthreads();
 
     // Refinement edges: every adjacency between a line and the one above that
@@ -673,12 +706,10 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
     // run is found for all runs at once: adding the run starts to the
     // columns without an edge carries each start up to its first edge.
     uint32_t cw = 0, c1w = 0, c2w = 0;  // edges in this thread's window (bit j = column wlo + j)
-    uint32_t lslw = 0, lsuw = 0;        // run starts of the two lines in the window
-    uint32_t prel = 0, preu = 0;        // runs of the two lines starting left of the window
-    if (wl > 0) {
-        const int l = wl;
-        const uint64_t T = top_row<D>(sh, l), B = bottom_row<D>(sh, l - 1);
-        const uint64_t lm = sh.LM[l], lsl = sh.LS[l], lsu = sh.LS[l - 1];
+    uint32_t lsuw = 0, preu = 0;        // as lslw and prel, of the line above
+    if (l > 0) {
+        const uint64_t T = D ? sh.M[2 * l] : lm, B = D ? sh.M[2 * l - 1] : sh.M[l - 1];
+        const uint64_t lu = line_of(sh, l - 1), lsu = lu & ~(lu << 1);
         uint64_t c0, c1 = 0, c2 = 0, e0, e2 = 0, first;
         if (!D) {
             const uint64_t o = T & B;
@@ -700,10 +731,7 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
         cw = (uint32_t)((c0 | c1 | c2) >> wlo) & WMASK;
         c1w = (uint32_t)(c1 >> wlo) & WMASK;
         c2w = (uint32_t)(c2 >> wlo) & WMASK;
-        lslw = (uint32_t)(lsl >> wlo) & WMASK;
         lsuw = (uint32_t)(lsu >> wlo) & WMASK;
-        const uint64_t left = ~(~0ull << wlo);
-        prel = sh.base[l] + popc64(lsl & left) - 1u;
         preu = sh.base[l - 1] + popc64(lsu & left) - 1u;
         // Column connection (coarse, Section 3.1.2): a run's first edge
         // joins it to the run holding its leftmost neighbour in the line
@@ -711,57 +739,78 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
         // that run was linked meanwhile, an ancestor with a smaller key).
         // Every run has at most one first edge, so every entry still has
         // one writer.
+        const uint32_t e0w = (uint32_t)(e0 >> wlo), e2w = (uint32_t)(e2 >> wlo);
+        const uint32_t lsun = (uint32_t)(lsu >> wlo >> 1);  // starts one column right
         for (uint32_t f = (uint32_t)(first >> wlo) & WMASK; f; f &= f - 1u) {
-            const int j = __builtin_ctz(f), p = wlo + j;
-            int u = p;  // upper pixel: same column, one left (i, i-1) or one right (i-1, i)
-            if (D && !((e0 >> p) & 1ull)) u = ((e2 >> p) & 1ull) ? p - 1 : p + 1;
-            const uint32_t lo = prel + __builtin_popcount(lslw & ((2u << j) - 1u));
-            const uint32_t up = sh.base[l - 1] + popc64(lsu & upto(u)) - 1u;
+            const uint32_t bit = f & (0u - f), upto_j = bit | (bit - 1u);
+            const uint32_t lo = prel + __builtin_popcount(lslw & upto_j);
+            // upper pixel: same column, one left (i, i-1) or one right (i-1, i)
+            uint32_t up = preu + __builtin_popcount(lsuw & upto_j);
+            if (D && !(e0w & bit)) {
+                if (e2w & bit) up -= (lsuw & bit) ? 1u : 0u;
+                else up += (lsun & bit) ? 1u : 0u;
+            }
             lds_st(sh.P + lo, lds_ld(sh.P + up));
         }
     }
+    // runs at the lower / upper pixel of the edge at `bit` of the window
+    auto edge_at = [&](uint32_t bit, uint32_t& lo, uint32_t& up) {
+        const uint32_t below = bit - 1u, upto_j = bit | below;
+        lo = prel + __builtin_popcount(lslw & ((c1w & bit) ? below : upto_j));  // (i-1, i)
+        up = preu + __builtin_popcount(lsuw & ((c2w & bit) ? below : upto_j));  // (i, i-1)
+    };
     // At most one edge per column, so the edge count of the window is a
-    // popcount; edges go to the list in any order.
+    // popcount; edges go to the list in any order.  The list takes what the
+    // runs leave of P (half of it on noise of any density); a thread whose
+    // edges do not fit keeps them, and voids the entries it was given.
+    uint32_t* EL = sh.P + R;
+    const uint32_t cap = (uint32_t)G::MAXR - R;
     if (cw) {
-        uint32_t off = atomicAdd(&sh.nedges, (uint32_t)__builtin_popcount(cw));
-        for (uint32_t r = cw; r; r &= r - 1u, ++off) {
-            const int j = __builtin_ctz(r);
-            const uint32_t bit = 1u << j;
-            // run holding the lower / upper pixel: runs starting at or left of it
-            const int jl = (c1w & bit) ? j : j + 1;  // (i-1, i): lower pixel one left
-            const int ju = (c2w & bit) ? j : j + 1;  // (i, i-1): upper pixel one left
-            sh.u.EL[off] = (prel + __builtin_popcount(lslw & ((1u << jl) - 1u))) |
-                           ((preu + __builtin_popcount(lsuw & ((1u << ju) - 1u))) << 16);
+        const uint32_t n = (uint32_t)__builtin_popcount(cw);
+        uint32_t off = atomicAdd(&sh.nedges, n);
+        if (off + n <= cap) {
+            for (; cw; cw &= cw - 1u, ++off) {
+                uint32_t lo, up;
+                edge_at(cw & (0u - cw), lo, up);
+                EL[off] = lo | (up << 16);
+            }
+        } else {
+            for (; off < cap; ++off) EL[off] = 0u;  // run 0 with itself
         }
     }
     __syncthreads();
-    const uint32_t E = sh.nedges;
+    const uint32_t E = min(sh.nedges, cap);
 
     // Label-equivalence unification: every run points at its current root
     // (the coarse links form chains down the lines), so that the
     // refinement's finds start from short paths.  The store is an atomic
     // min: a merge of the refinement may already have linked that run.
-    for (uint32_t id = tid; id < R; id += NT)
+    for (uint32_t id = tid; id < R; id += NTL)
         __hip_atomic_fetch_min(sh.P + id, pfind(sh.P, id), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
 
     // Refinement: the paper's merge on every listed edge.
-    for (uint32_t k = tid; k < E; k += NT) {
-        const uint32_t ed = sh.u.EL[k];
+    for (uint32_t k = tid; k < E; k += NTL) {
+        const uint32_t ed = EL[k];
         punion(sh.P, ed & 0xffffu, ed >> 16);
+    }
+    for (; cw; cw &= cw - 1u) {
+        uint32_t lo, up;
+        edge_at(cw & (0u - cw), lo, up);
+        punion(sh.P, lo, up);
     }
     __syncthreads();
 
     // Unification again: every run points straight at its final local root.
-    for (uint32_t id = tid; id < R; id += NT) lds_st(sh.P + id, pfind(sh.P, id));
+    for (uint32_t id = tid; id < R; id += NTL) lds_st(sh.P + id, pfind(sh.P, id));
     __syncthreads();
 
-    // Border slots (slots tid, tid + NT, ...): local root of each border pixel.
-    bool fg[SPT];
-    uint32_t root[SPT], rkey[SPT];
+    // Border slots (slots tid, tid + NTL, ...): local root of each border pixel.
+    bool fg[G::SPL];
+    uint32_t root[G::SPL], rkey[G::SPL];
 #pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-        const int s = tid + k * NT;
+    for (int k = 0; k < G::SPL; ++k) {
+        const int s = tid + k * NTL;
         fg[k] = false;
         root[k] = rkey[k] = 0;
         if (s < NSLOTS) {
@@ -769,7 +818,10 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
             slot_xy(s, sx, sy);
             fg[k] = (sh.M[sy] >> sx) & 1ull;
             if (fg[k]) {
-                const uint32_t v = lds_ld(sh.P + run_id<D>(sh, D ? sy >> 1 : sy, sx));
+                const int sl = D ? sy >> 1 : sy;
+                const uint64_t sm = line_of(sh, sl);
+                const uint32_t v =
+                    lds_ld(sh.P + (sh.base[sl] + popc64(sm & ~(sm << 1) & upto(sx)) - 1u));
                 root[k] = pk_id(v);
                 rkey[k] = pk_key(v);
             }
@@ -779,9 +831,9 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
     // Elect the smallest slot of each border component as its representative
     // (an atomic max on the root entry, which is no longer needed as a parent).
 #pragma unroll
-    for (int k = 0; k < SPT; ++k)
+    for (int k = 0; k < G::SPL; ++k)
         if (fg[k])
-            __hip_atomic_fetch_max(sh.P + root[k], REP_TAG | (uint32_t)(NSLOTS - 1 - (tid + k * NT)),
+            __hip_atomic_fetch_max(sh.P + root[k], REP_TAG | (uint32_t)(NSLOTS - 1 - (tid + k * NTL)),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
 
@@ -789,8 +841,8 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
     // the raster position of the component's smallest pixel.
     const int64_t sbase = T * NSLOTS;
 #pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-        const int s = tid + k * NT;
+    for (int k = 0; k < G::SPL; ++k) {
+        const int s = tid + k * NTL;
         if (s >= NSLOTS) continue;
         int32_t node = -1;
         if (fg[k]) {
@@ -808,7 +860,7 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
     // Run table: interior components store their root's tile key; border
     // components store their representative slot.
     uint16_t* rt = ws.runtab + T * RUNTAB_PER_TILE;
-    for (uint32_t id = tid; id < R; id += NT) {
+    for (uint32_t id = tid; id < R; id += NTL) {
         const uint32_t v = lds_ld(sh.P + id);
         uint16_t ent;
         if (v & REP_TAG) {
@@ -822,37 +874,35 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
     }
 }
 
-// Each workgroup labels tiles blockIdx.x, +gridDim.x, ... and loads the next
-// tile's bytes while labelling the current one, so that with a grid smaller
-// than the tile count (tile_grid) the load latency overlaps the LDS work.
-static_assert(TILE_ROWS * 4 == NT, "one sixteen-byte chunk per thread");
-template <int D>
-__global__ __launch_bounds__(NT) void k_local(BatchArgs b, Workspace ws)
+// One tile per workgroup: the dispatcher balances tiles of unequal cost.
+template <int D, int WPL>
+__global__ __launch_bounds__((LGeo<D, WPL>::NTL)) void k_local(BatchArgs b, Workspace ws)
 {
+    using G = LGeo<D, WPL>;
     __shared__ LocalShared<D> sh;
     const int tid = threadIdx.x;
-    int64_t T = blockIdx.x;
-    if (T >= b.ntiles) return;
-    ImageArgs a = batch_image(b, tile_image(b, T));
-    int t = (int)(T - a.tbase);
-    Chunk raw = fetch_chunk(a, t, tid);
-    for (; T < b.ntiles; T += gridDim.x) {
-        sh.u.h[tid] = (uint16_t)chunk_mask(raw);
-        const int64_t TN = T + gridDim.x;
-        ImageArgs an = a;
-        int tn = 0;
-        if (TN < b.ntiles) {
-            an = batch_image(b, tile_image(b, TN));
-            tn = (int)(TN - an.tbase);
-            raw = fetch_chunk(an, tn, tid);
-        }
-        __syncthreads();
-        local_tile<D>(a, ws, sh, t, tid);
-        __syncthreads();
-        a = an;
-        t = tn;
-    }
+    const int64_t T = blockIdx.x;
+    const ImageArgs a = batch_image(b, tile_image(b, T));
+    const int t = (int)(T - a.tbase);
+    Chunk raw[G::CPT];
+#pragma unroll
+    for (int q = 0; q < G::CPT; ++q) raw[q] = fetch_chunk(a, t, tid + q * G::NTL);
+    uint16_t* h = reinterpret_cast<uint16_t*>(sh.M);
+#pragma unroll
+    for (int q = 0; q < G::CPT; ++q) h[tid + q * G::NTL] = (uint16_t)chunk_mask(raw[q]);
+    __syncthreads();
+    local_tile<D, WPL>(a, ws, sh, t, tid);
 }
+
+// Threads per line: with few tiles in a launch its time is one tile's latency,
+// and many threads per tile shorten it; with many tiles it is the instructions
+// issued, and the arithmetic repeated by every thread of a line counts
+// (whole calls, 8-connected Bernoulli 0.41 of 1077 x 1913, 2048^2 and 4096^2:
+// 34.9, 43.3 and 77 us with the first, 39.4, 46.2 and 72.5 with the second).
+template <int D>
+constexpr int WPL_FEW = D ? 8 : 4;
+template <int D>
+constexpr int WPL_MANY = D ? 4 : 2;
 
 // ---------------------------------------------------------------------------
 // block merge (Section 3.2), in two levels
@@ -3189,20 +3239,24 @@ static unsigned resident_blocks(K kernel, int threads)
     return n;
 }
 
-// Launch shape of k_local and k_final: persistent (one workgroup per
-// resident slot, the next tile's loads in flight while the current one is
-// labelled) or one workgroup per tile (the dispatcher balances tiles of
-// unequal cost, which a fixed round-robin over many tiles does not).  The
-// caller may fix the choice (a tuned policy); otherwise the built-in rule
-// holds: k_local goes per tile beyond four times the resident workgroups
-// (8192^2 with 64-row tiles: 142 -> 126 us on Bernoulli 0.5, 111 -> 79 us on
-// the spiral), k_final stays persistent.
-// kernel 0 = k_local, 1 = k_final
-static unsigned tile_grid(int kernel, const BatchArgs& b, unsigned resident, GridChoice g)
+// Launch shape of k_final: persistent (one workgroup per resident slot, the
+// next tile's loads in flight while the current one is labelled; the built-in
+// choice) or one workgroup per tile, if a tuned policy says so.
+static unsigned final_grid(const BatchArgs& b, unsigned resident, GridChoice g)
 {
-    const int v = kernel == 0 ? g.local : g.final_;
-    const bool per_tile = v >= 0 ? v == 1 : (kernel == 0 && b.ntiles > 4 * (int64_t)resident);
-    return per_tile ? (unsigned)b.ntiles : (unsigned)std::min<int64_t>(b.ntiles, resident);
+    return g.final_ == 1 ? (unsigned)b.ntiles : (unsigned)std::min<int64_t>(b.ntiles, resident);
+}
+
+// Launches k_local with the split for few tiles or, beyond the workgroups of
+// that split that the device holds at once, the one for many.
+template <int D>
+static void launch_local(const BatchArgs& b, const Workspace& ws, hipStream_t st)
+{
+    constexpr int FEW = WPL_FEW<D>, MANY = WPL_MANY<D>;
+    if (b.ntiles > (int64_t)resident_blocks(k_local<D, FEW>, LGeo<D, FEW>::NTL))
+        k_local<D, MANY><<<(unsigned)b.ntiles, (LGeo<D, MANY>::NTL), 0, st>>>(b, ws);
+    else
+        k_local<D, FEW><<<(unsigned)b.ntiles, (LGeo<D, FEW>::NTL), 0, st>>>(b, ws);
 }
 
 int64_t image_groups(int ntx, int nty, bool direct)
@@ -3230,12 +3284,11 @@ static hipError_t launch_all(const BatchArgs& b, const Workspace& ws, hipStream_
 #if CCL_TILE_ROWS != 64
     if (stats) return hipErrorInvalidValue;  // statistics use the built-in tile height
 #endif
-    const unsigned lgrid = tile_grid(0, b, resident_blocks(k_local<D>, NT), grid);
     timer_begin(timer, KIND_LOCAL, st);
-    k_local<D><<<lgrid, NT, 0, st>>>(b, ws);
+    launch_local<D>(b, ws, st);
     timer_end(timer, KIND_LOCAL, st);
     if (local_only) {
-        const unsigned fgrid = tile_grid(1, b, resident_blocks(k_final<D, true, false>, NT), grid);
+        const unsigned fgrid = final_grid(b, resident_blocks(k_final<D, true, false>, NT), grid);
         timer_begin(timer, KIND_FINAL, st);
         k_final<D, true, false><<<fgrid, NT, 0, st>>>(b, ws, none);
         timer_end(timer, KIND_FINAL, st);
@@ -3254,15 +3307,14 @@ static hipError_t launch_all(const BatchArgs& b, const Workspace& ws, hipStream_
         timer_end(timer, KIND_SEAM, st);
     }
     if (!stats) {
-        const unsigned fgrid =
-            tile_grid(1, b, resident_blocks(k_final<D, false, false>, NT), grid);
+        const unsigned fgrid = final_grid(b, resident_blocks(k_final<D, false, false>, NT), grid);
         timer_begin(timer, KIND_FINAL, st);
         k_final<D, false, false><<<fgrid, NT, 0, st>>>(b, ws, none);
         timer_end(timer, KIND_FINAL, st);
         return hipGetLastError();
     }
 #if CCL_TILE_ROWS == 64
-    const unsigned fgrid = tile_grid(1, b, resident_blocks(k_final<D, false, true>, NT), grid);
+    const unsigned fgrid = final_grid(b, resident_blocks(k_final<D, false, true>, NT), grid);
     timer_begin(timer, KIND_FINAL, st);
     k_final<D, false, true><<<fgrid, NT, 0, st>>>(b, ws, *stats);
     timer_end(timer, KIND_FINAL, st);
@@ -3303,10 +3355,9 @@ static hipError_t replay_all(const BatchArgs& b, const Workspace& ws, hipStream_
 {
     if (b.ntiles <= 0) return hipSuccess;
     if (kind == KIND_LOCAL) {
-        const unsigned g = tile_grid(0, b, resident_blocks(k_local<D>, NT), grid);
-        for (int r = 0; r < reps; ++r) k_local<D><<<g, NT, 0, st>>>(b, ws);
+        for (int r = 0; r < reps; ++r) launch_local<D>(b, ws, st);
     } else if (kind == KIND_FINAL) {
-        const unsigned g = tile_grid(1, b, resident_blocks(k_final<D, false, false>, NT), grid);
+        const unsigned g = final_grid(b, resident_blocks(k_final<D, false, false>, NT), grid);
         for (int r = 0; r < reps; ++r) k_final<D, false, false><<<g, NT, 0, st>>>(b, ws, StatsWs{});
     } else {
         return hipErrorInvalidValue;
@@ -3345,7 +3396,7 @@ hipError_t launch_ablation(const BatchArgs& b, const Workspace& ws, hipStream_t 
     else if (b.nseamwg > 0)
         k_seam<0, BX, BY><<<(unsigned)b.nseamwg, SEAM_WG, 0, st>>>(b, ws);
     const unsigned fgrid =
-        tile_grid(1, b, resident_blocks(k_final<0, false, false>, NT), GridChoice{});
+        final_grid(b, resident_blocks(k_final<0, false, false>, NT), GridChoice{});
     k_final<0, false, false><<<fgrid, NT, 0, st>>>(b, ws, StatsWs{});
     return hipGetLastError();
 }

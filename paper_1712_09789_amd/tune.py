@@ -2,19 +2,18 @@
 
 The paper's one tuning knob is the block shape (Section 4.1, effectiveness
 of coarse labelling).  The library is built for tiles 64 pixels wide and
-32, 64 or 128 rows high, and each of its two per-tile kernels (the local
-step and the final relabel) runs either on a persistent grid or with one
-workgroup per tile (``ccl_set_launch_policy`` in include/ccl.h).  Which is
-fastest depends on the image size, on whether a launch holds one image or
-many, and on the connectivity, so for every launch class (one image /
-several), pixel bucket and connectivity this module
+32, 64 or 128 rows high, and its final relabel runs either on a persistent
+grid or with one workgroup per tile (``ccl_set_launch_policy`` in
+include/ccl.h).  Which is fastest depends on the image size, on whether a
+launch holds one image or many, and on the connectivity, so for every launch
+class (one image / several), pixel bucket and connectivity this module
 
 1. times every tile height with the built-in grids, on two synthetic
    contents of the bucket's size (Bernoulli(0.5) noise, the paper's worst
    density, and box-smoothed thresholded noise for large regions); a
    batch class uses images with sides log-uniform in [64, 2048], the
    batched workload's size mix;
-2. times the four grid combinations with the fastest height;
+2. times both grids with the fastest height;
 3. keeps a non-built-in choice only if it beats the built-in one (64 rows,
    built-in grids) by at least MARGIN, so that noise does not decide,
 
@@ -35,7 +34,7 @@ import torch
 
 import paper_1712_09789_amd.ccl as ccl
 
-GRIDS = ((0, 0), (0, 1), (1, 0), (1, 1))  # (local, final): 0 = persistent, 1 = per tile
+GRIDS = ((-1, 0), (-1, 1))  # (local, final): final 0 = persistent, 1 = per tile
 MARGIN = 0.02  # a choice must beat the built-in one by this fraction
 BATCH_SIDES = (64, 2048)  # side range of a batch class's images (log-uniform)
 MAX_BATCH_IMAGES = 4096
@@ -90,8 +89,8 @@ def tune(reps: int = 5, buckets: list[int] | None = None, seed: int = 0) -> dict
     """Time the tile heights and grids per (launch class, bucket,
     connectivity), apply the choices and return {"arch", "buckets",
     "shapes", "choices": [{batch, bucket, connectivity, pixels, tile_rows,
-    local, final, us: {config: microseconds}}]} (tile_rows 0 and local =
-    final = -1: the built-in choice).  `buckets` limits the buckets tuned
+    local, final, us: {config: microseconds}}]} (tile_rows 0 and final = -1:
+    the built-in choice; local is always -1).  `buckets` limits the buckets tuned
     (the others keep their current setting)."""
     bounds = ccl.launch_buckets()
     shapes_built = ccl.tile_shapes()
