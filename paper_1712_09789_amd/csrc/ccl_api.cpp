@@ -306,16 +306,16 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
     return c;
 }
 
-// Launches of at most this many pixels with a seam between merge groups unite
-// their tiles across every seam in one kernel (k_seam) instead of two levels
+// Launches of at most this many tiles with a seam between merge groups unite
+// them across every seam in one kernel (k_seam) instead of two levels
 // (k_block, then k_seam between groups): below it the merge is two launches'
 // latency, above it the longer chains of a forest over all tiles cost more
-// than the launch.  640 x 480 and 2048^2 blobs, Bernoulli 0.41 and
-// serpentine at 8-connectivity: 18.4, 24.4 and 19.9 us against 22.7, 31.8 and
-// 22.6; 27.5, 41.0, 34.8 against 31.9, 43.7, 31.7; 3000^2: 39.1, 63.1, 67.6
-// against 42.4, 61.3, 48.1.  Images of one group keep k_block, which is all
-// their merge and leaves their forest flat.
-constexpr int64_t DIRECT_PX = int64_t(1) << 22;
+// than the launch.  640 x 480 (40 tiles of 128 rows) and 2048^2 (512) blobs,
+// Bernoulli 0.41 and serpentine at 8-connectivity: 18.4, 24.4 and 19.9 us
+// against 22.7, 31.8 and 22.6; 27.5, 41.0, 34.8 against 31.9, 43.7, 31.7;
+// 3000^2 (1128): 39.1, 63.1, 67.6 against 42.4, 61.3, 48.1.  Images of one
+// group keep k_block, which is all their merge and leaves their forest flat.
+constexpr int64_t DIRECT_TILES = 512;
 
 // Sizes of one connectivity class of a batch.
 struct ClassLayout {
@@ -337,12 +337,12 @@ static int layout_class(std::vector<ImageArgs>& imgs, int conn, const ShapeOps& 
     L.toff.assign(n + 1, 0);
     L.goff.assign(n + 1, 0);
     L.soff.assign(n + 1, 0);
-    int64_t px = 0, seams = 0;
+    int64_t tiles = 0, seams = 0;
     for (const ImageArgs& a : imgs) {
-        px += (int64_t)a.H * a.W;
+        tiles += (int64_t)a.ntx * a.nty;
         seams += ops.image_seam_items(a.ntx, a.nty, a.H, a.W, conn, false);
     }
-    L.direct = seams > 0 && px <= DIRECT_PX;
+    L.direct = seams > 0 && tiles <= DIRECT_TILES;
     for (int i = 0; i < n; ++i) {
         ImageArgs& a = imgs[i];
         a.tbase = L.toff[i];

@@ -1462,7 +1462,7 @@ __device__ __forceinline__ uint32_t bit_position_sum(uint64_t m)
 template <int D>
 struct StatsShared : Lines<D> {
     uint16_t RL[Geo<D>::MAXR];
-    alignas(16) uint16_t ent[RUNTAB_PER_TILE];  // the tile's run table
+    alignas(16) uint16_t ent[Geo<D>::MAXR];  // the tile's run table
     // Per component part, in tile-local coordinates, three words that take
     // one atomic each per run: the packed sums (area | sum x << 13 | sum y
     // << 31; a tile's totals fit 13, 18 and 18 bits, so no field carries into
@@ -1527,11 +1527,17 @@ __device__ __forceinline__ int64_t tile_number(const SH& sh, int ky, int kx)
 // pixel writes the entry's starting values (label, top row, empty sums and
 // box).  Components whose smallest pixel lies in this tile are numbered
 // from the tile's staged row counts; the partial records carry the label.
-constexpr int ST = 1024;  // k_stats threads per tile (its LDS allows two workgroups per
-                          // compute unit, so a wide workgroup keeps the unit busy)
+// Threads per tile: at 4-connectivity its LDS allows two workgroups per
+// compute unit, and a wide one keeps the unit busy; at 8 it allows four, and
+// four tiles of 512 threads wait less at barriers than two of 1024 (4000^2
+// Bernoulli 0.41, whole calls: 149 -> 136 us; 256 threads 138; 4-connected
+// with 512 threads 136 against 135, with 256 147).
 template <int D>
-__global__ __launch_bounds__(ST) void k_stats(BatchArgs b, Workspace ws, StatsWs st)
+constexpr int STATS_T = D ? 512 : 1024;
+template <int D>
+__global__ __launch_bounds__(STATS_T<D>) void k_stats(BatchArgs b, Workspace ws, StatsWs st)
 {
+    constexpr int ST = STATS_T<D>;
     __shared__ StatsShared<D> sh;
     const int tid = threadIdx.x;
     const int64_t T = blockIdx.x;
@@ -1552,8 +1558,8 @@ __global__ __launch_bounds__(ST) void k_stats(BatchArgs b, Workspace ws, StatsWs
     }
     // the whole run table, in the same round trip as the loads above (its
     // entries past the tile's run count are never read)
-    static_assert(RUNTAB_PER_TILE % 8 == 0 && RUNTAB_PER_TILE / 8 <= ST, "one chunk per thread");
-    if (tid < RUNTAB_PER_TILE / 8)
+    static_assert(Geo<D>::MAXR % 8 == 0 && Geo<D>::MAXR / 8 <= ST, "one chunk per thread");
+    if (tid < Geo<D>::MAXR / 8)
         reinterpret_cast<uint4*>(sh.ent)[tid] = ld_global16(ws.runtab + T * RUNTAB_PER_TILE + 8 * tid);
     if (tid == 0) sh.nrec = 0u;
     __syncthreads();
@@ -3322,7 +3328,7 @@ static hipError_t launch_all(const BatchArgs& b, const Workspace& ws, hipStream_
     k_scan1<<<(unsigned)stats->nblk, SCAN_T, 0, st>>>(*stats);
     k_scan2<<<1, SCAN_T, 0, st>>>(*stats);
     if (stats->capacity > 0) {
-        k_stats<D><<<(unsigned)b.ntiles, ST, 0, st>>>(b, ws, *stats);
+        k_stats<D><<<(unsigned)b.ntiles, STATS_T<D>, 0, st>>>(b, ws, *stats);
         const ImageArgs& a = b.one;
         static_assert(TW == TILE_ROWS, "square tiles: merge regions are squares of tiles");
         k_stats_merge<<<(unsigned)(stats->g1x * stats->g1y), MERGE_T, 0, st>>>(

@@ -1,6 +1,5 @@
-"""The one-level merge of small launches (at most 2^22 pixels with a seam
-between merge groups) against the oracle, and both sides of that line
-(tolerance 0)."""
+"""The one-level merge of small launches (at most 512 tiles with a seam between
+merge groups) against the oracle, and both sides of that line (tolerance 0)."""
 import numpy as np
 import pytest
 
@@ -11,7 +10,7 @@ from seam_atlas import Layout
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
-SIZE = 2048  # 2^22 pixels: the largest square launch that merges in one level
+SIZE = {32: 1024, 64: 1024, 128: 2048}  # at most 512 tiles, by tile height
 GROUP_PX = 256
 
 
@@ -27,10 +26,11 @@ def ccl():
 @pytest.mark.parametrize("conn", [4, 8])
 def test_patterns_on_every_seam_kind(ccl, conn, rows):
     cols = ccl.tile_shape()[1]
-    L = Layout(SIZE, SIZE, rows, cols, (GROUP_PX // rows, GROUP_PX // cols), conn, "cuda")
+    size = SIZE[rows]
+    L = Layout(size, size, rows, cols, (GROUP_PX // rows, GROUP_PX // cols), conn, "cuda")
     for n in np.linspace(0, L.n_images - 1, 12).astype(int):
         pid = L.assemble(int(n))
-        got = ccl.label(L.img.view(SIZE, SIZE), conn, tile_rows=rows).view(-1)
+        got = ccl.label(L.img.view(size, size), conn, tile_rows=rows).view(-1)
         bad = torch.nonzero(got != L.want)
         assert len(bad) == 0, f"image {n}: {L.describe(pid, int(bad[0]))}"
 
@@ -47,7 +47,7 @@ def test_both_sides_of_the_line(ccl, shape, conn):
 
 @pytest.mark.parametrize("conn", [4, 8])
 def test_small_images_merged_in_groups(ccl, conn):
-    # beside an image of more than 2^22 pixels the same small images take the
+    # beside an image of more than 512 tiles the same small images take the
     # two-level merge
     imgs = [wl.bernoulli(300, 517, 0.5, seed=1), wl.spiral(257, 600), wl.full(520, 130),
             wl.blobs(700, 301, 4.0, seed=2)]
