@@ -458,6 +458,16 @@ __device__ __forceinline__ void slot_xy(int s, int& x, int& y)
     else { x = TW - 1; y = s - 2 * TW - TILE_ROWS; }
 }
 
+// Slot table entries: -1 for a background pixel, else a forest node of its
+// component.  Between the local step and a merge inside groups they name the
+// component within its tile, all that merge needs: the tile key of its
+// smallest pixel << 9 | its representative slot.
+static_assert(NSLOTS <= 512 && ((TILE_ROWS * TW) << 9) <= (1 << 30), "slot entry fields");
+__device__ __forceinline__ int32_t slot_entry(uint32_t key, uint32_t rep)
+{
+    return (int32_t)((key << 9) | rep);
+}
+
 // Run-table entry flag: the run's component touches the tile border (low
 // bits = its representative border slot; otherwise the entry is the tile
 // position of the component's smallest pixel).
@@ -608,7 +618,7 @@ __device__ __forceinline__ uint32_t chunk_mask(const Chunk& k)
 // slower on noise (31.4), four threads per line at 4-connectivity too (112).
 template <int D, int WPL>
 __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<D>& sh, int t,
-                           int tid)
+                           int tid, bool grouped)
 {
     using G = LGeo<D, WPL>;
     constexpr int NTL = G::NTL;
@@ -837,24 +847,27 @@ __device__ void local_tile(const ImageArgs& a, const Workspace& ws, LocalShared<
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
 
-    // ID conversion (Section 3.1.4): the representative's forest node carries
-    // the raster position of the component's smallest pixel.
+    // ID conversion (Section 3.1.4).  Where a merge inside groups follows, it
+    // makes the forest and the node ids from the tile keys; else the
+    // representative's forest node takes the raster position of the
+    // component's smallest pixel here.
     const int64_t sbase = T * NSLOTS;
+    const bool nodes = !grouped || (a.ntx == 1 && a.nty == 1);
 #pragma unroll
     for (int k = 0; k < G::SPL; ++k) {
         const int s = tid + k * NTL;
         if (s >= NSLOTS) continue;
-        int32_t node = -1;
+        int32_t ent = -1;
         if (fg[k]) {
             const int rep = NSLOTS - 1 - (int)pk_id(lds_ld(sh.P + root[k]));
-            node = (int32_t)(sbase + rep);
-            if (rep == s) {
+            ent = nodes ? (int32_t)sbase + rep : slot_entry(rkey[k], (uint32_t)rep);
+            if (nodes && rep == s) {
                 const uint32_t gkey = (uint32_t)((int64_t)(gy0 + (int)(rkey[k] / TW)) * a.W +
                                                  gx0 + (int)(rkey[k] % TW));
-                ws.forest[node] = ((uint64_t)gkey << 32) | (uint32_t)node;
+                ws.forest[ent] = ((uint64_t)gkey << 32) | (uint32_t)ent;
             }
         }
-        ws.slots[sbase + s] = node;
+        ws.slots[sbase + s] = ent;
     }
 
     // Run table: interior components store their root's tile key; border
@@ -891,7 +904,7 @@ __global__ __launch_bounds__((LGeo<D, WPL>::NTL)) void k_local(BatchArgs b, Work
 #pragma unroll
     for (int q = 0; q < G::CPT; ++q) h[tid + q * G::NTL] = (uint16_t)chunk_mask(raw[q]);
     __syncthreads();
-    local_tile<D, WPL>(a, ws, sh, t, tid);
+    local_tile<D, WPL>(a, ws, sh, t, tid, b.ngroups > 0);
 }
 
 // Threads per line: with few tiles in a launch its time is one tile's latency,
@@ -1007,12 +1020,17 @@ __device__ __forceinline__ SeamNodes vseam_nodes(const ImageArgs& a, const int32
 
 constexpr int NTB = 1024;  // threads per merge-group workgroup
 
+// Bound by latency and instruction issue: a group is one workgroup, whose 64-slot
+// spans of a tile are wavefronts, so that tile positions and addresses are
+// scalar.  All it reads are the slot tables, whose entries carry the tile key
+// of their component (with the keys in the forest, read besides and divided by
+// the width, and addresses per lane: 24 us on 8192^2 Bernoulli 0.6, 44 on 256
+// mixed images, 10 at 4096^2; now 18, 36 and 8).
 template <int D>
 __global__ __launch_bounds__(NTB) void k_block(BatchArgs b, Workspace ws)
 {
-    __shared__ uint32_t P[BN];           // (group key << 16) | group index
-    __shared__ int32_t S[BN];            // the group's slot tables (node ids, -1 = bg)
-    __shared__ uint32_t isrep[BN / 32];  // group indices that are forest nodes
+    __shared__ uint32_t P[BN];  // (group key << 16) | group index
+    __shared__ int32_t S[BN];   // group index of the component at each slot, -1 = bg
     const int tid = threadIdx.x;
     const int img = b.n == 1 ? 0 : ld_uniform(b.group_img + blockIdx.x);
     const ImageArgs a = batch_image(b, img);
@@ -1020,125 +1038,110 @@ __global__ __launch_bounds__(NTB) void k_block(BatchArgs b, Workspace ws)
     const int nbx = (a.ntx + BX - 1) / BX;
     const int tx0 = (g % nbx) * BX, ty0 = (g / nbx) * BY;
     const int px0 = tx0 * TW, py0 = ty0 * TILE_ROWS;
+    const int tile0 = (int)a.tbase + ty0 * a.ntx + tx0;  // the group's first global tile
 
-    // The group's slot tables and forest entries: all loads are issued before
-    // any is used (one round trip instead of one per pass).  Tiles past the
-    // image edge read the group's first tile and count as background.  Nodes
-    // are keyed by the position of their smallest pixel relative to the group
-    // origin (same order as raster position).
-    constexpr int PER = BN / NTB;
-    static_assert(BN % NTB == 0 && NTB % 64 == 0, "whole wavefronts per pass");
-    int32_t nd[PER];
-    uint32_t fk[PER];
-    int64_t ix[PER];
-    bool in[PER];
+    // Span w = 64 slots of tile w / SPANS of the group.  Tiles past the image
+    // edge count as background.  Components are keyed by the position of their
+    // smallest pixel relative to the group origin (same order as raster
+    // position).
+    constexpr int SPANS = NSLOTS / 64, PER = BN / NTB;
+    static_assert(NSLOTS % 64 == 0 && BN % NTB == 0, "whole wavefronts");
+    const int lane = tid & 63;
+    const int w0 = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+    auto tile_of = [&](int ti) { return tile0 + (ti / BX) * a.ntx + ti % BX; };
+    auto inside = [&](int ti) { return tx0 + ti % BX < a.ntx && ty0 + ti / BX < a.nty; };
+    int32_t gi[PER];  // group index of the component at each of this thread's slots
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int li = tid + k * NTB;
-        const int ti = li / NSLOTS, sl = li % NSLOTS;
-        const int tx = tx0 + ti % BX, ty = ty0 + ti / BX;
-        in[k] = tx < a.ntx && ty < a.nty;
-        ix[k] = (a.tbase + (int64_t)(in[k] ? ty : ty0) * a.ntx + (in[k] ? tx : tx0)) * NSLOTS + sl;
-        nd[k] = ws.slots[ix[k]];
-        fk[k] = (uint32_t)(ws.forest[ix[k]] >> 32);
+        const int w = w0 + k * (NTB / 64), ti = w / SPANS, sl = (w % SPANS) * 64 + lane;
+        gi[k] = inside(ti) ? ws.slots[(int64_t)tile_of(ti) * NSLOTS + sl] : -1;
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int li = tid + k * NTB;
-        const int32_t node = in[k] ? nd[k] : -1;
-        const bool rep = node == (int32_t)ix[k];
+        const int w = w0 + k * (NTB / 64), ti = w / SPANS, li = w * 64 + lane;
+        const uint32_t v = (uint32_t)gi[k], key = (v >> 9) & (TILE_ROWS * TW - 1);
+        if (gi[k] != -1) gi[k] = ti * NSLOTS + (int)(v & 511u);
         // every entry gets a value; only those of representatives are read
-        uint32_t gy, gx;
-        divmod_w(fk[k], (uint32_t)a.W, a.wmagic, gy, gx);
-        P[li] = pk((gy - py0) * BPX + (gx - px0), li);
-        const uint64_t bal = __ballot(rep);
-        if ((tid & 63) == 0) {
-            isrep[li >> 5] = (uint32_t)bal;
-            isrep[(li >> 5) + 1] = (uint32_t)(bal >> 32);
-        }
-        S[li] = node;
+        P[li] = pk(((ti / BX) * TILE_ROWS + key / TW) * BPX + (ti % BX) * TW + key % TW, li);
+        S[li] = gi[k];
     }
     __syncthreads();
 
-    // Node id -> group index, for a node of the group tile (txl, tyl).
-    auto gidx = [&](int32_t node, int txl, int tyl) {
-        const int ti = tyl * BX + txl;
-        const int64_t base = (a.tbase + (int64_t)(ty0 + tyl) * a.ntx + tx0 + txl) * NSLOTS;
-        return (uint32_t)(ti * NSLOTS + (int)(node - base));
+    // Seams between tile columns inside the group, then between tile rows;
+    // diagonal edges that reach the group to the left belong to k_seam.
+    // (Slots outside the image are background.)
+    constexpr int NV = (BX - 1) * BPY, NH = (BY - 1) * BPX;
+    for (int it = tid; it < NV + NH; it += NTB) {
+        int32_t ap = -1, ac, bp = -1, bc;
+        if (it < NV) {
+            const int j = it / BPY + 1, yy = it % BPY;
+            const int tyl = yy / TILE_ROWS, yl = yy % TILE_ROWS;
+            const int32_t* L = S + (tyl * BX + j - 1) * NSLOTS + 2 * TW + TILE_ROWS;
+            const int32_t* Rr = S + (tyl * BX + j) * NSLOTS + 2 * TW;
+            ac = L[yl];
+            bc = Rr[yl];
+            if (yl > 0) {
+                ap = L[yl - 1];
+                bp = Rr[yl - 1];
+            }
+        } else {
+            const int k = (it - NV) / BPX + 1, xx = (it - NV) % BPX;
+            // bottom row of the upper tile, top row of the lower one
+            auto A = [&](int x) { return S[((k - 1) * BX + x / TW) * NSLOTS + TW + x % TW]; };
+            auto B = [&](int x) { return S[(k * BX + x / TW) * NSLOTS + x % TW]; };
+            ac = A(xx);
+            bc = B(xx);
+            if (xx > 0) {
+                ap = A(xx - 1);
+                bp = B(xx - 1);
+            }
+        }
+        const int m = seam_edges<D>(ap, ac, bp, bc);
+        if (m & E_II) punion(P, (uint32_t)ac, (uint32_t)bc);
+        if (m & E_PI) punion(P, (uint32_t)ap, (uint32_t)bc);
+        if (m & E_IP) punion(P, (uint32_t)ac, (uint32_t)bp);
+    }
+    __syncthreads();
+
+    // Every node of the group now points at its group root in the forest.
+    // Slots take node ids: the border slots that k_seam reads (the group's
+    // outer rows and columns, and the end pixels of tile rows at the group's
+    // left and right columns) that of the group root, the others that of
+    // their representative.  Entries of slots that are no representative are
+    // never read; they are written all the same, so that the forest leaves
+    // the chip in whole cache lines (entries of representatives alone made
+    // the relabel that reads them wait: 74 -> 82 us on 8192^2 Bernoulli 0.6,
+    // 41 -> 54 on 32 frames).
+    auto node_of = [&](uint32_t l) {
+        const int tj = (int)(l / NSLOTS);
+        return (uint32_t)tile_of(tj) * NSLOTS + l % NSLOTS;
     };
-    // seams between tile columns inside the group
-    for (int it = tid; it < (BX - 1) * BPY; it += NTB) {
-        const int j = it / BPY + 1, yy = it % BPY;
-        if (tx0 + j >= a.ntx || py0 + yy >= a.H) continue;
-        const int tyl = yy / TILE_ROWS, yl = yy % TILE_ROWS;
-        const int32_t* L = S + (tyl * BX + j - 1) * NSLOTS + 2 * TW + TILE_ROWS;
-        const int32_t* Rr = S + (tyl * BX + j) * NSLOTS + 2 * TW;
-        const int32_t ac = L[yl], bc = Rr[yl];
-        const int32_t ap = yl > 0 ? L[yl - 1] : -1, bp = yl > 0 ? Rr[yl - 1] : -1;
-        const int m = seam_edges<D>(ap, ac, bp, bc);
-        if (m & E_II) punion(P, gidx(ac, j - 1, tyl), gidx(bc, j, tyl));
-        if (m & E_PI) punion(P, gidx(ap, j - 1, tyl), gidx(bc, j, tyl));
-        if (m & E_IP) punion(P, gidx(ac, j - 1, tyl), gidx(bp, j, tyl));
-    }
-    // seams between tile rows inside the group; diagonal edges that reach the
-    // group to the left belong to k_seam
-    for (int it = tid; it < (BY - 1) * BPX; it += NTB) {
-        const int k = it / BPX + 1, xx = it % BPX;
-        if (ty0 + k >= a.nty || px0 + xx >= a.W) continue;
-        const int txl = xx / TW, xl = xx % TW;
-        const int32_t* A = S + ((k - 1) * BX + txl) * NSLOTS + TW;  // bottom row of the upper tile
-        const int32_t* B = S + (k * BX + txl) * NSLOTS;             // top row of the lower tile
-        const int32_t ac = A[xl], bc = B[xl];
-        int32_t ap = -1, bp = -1;
-        int txp = txl;
-        if (xx > 0) {
-            txp = (xx - 1) / TW;
-            const int xp = (xx - 1) % TW;
-            ap = S[((k - 1) * BX + txp) * NSLOTS + TW + xp];
-            bp = S[(k * BX + txp) * NSLOTS + xp];
-        }
-        const int m = seam_edges<D>(ap, ac, bp, bc);
-        if (m & E_II) punion(P, gidx(ac, txl, k - 1), gidx(bc, txl, k));
-        if (m & E_PI) punion(P, gidx(ap, txp, k - 1), gidx(bc, txl, k));
-        if (m & E_IP) punion(P, gidx(ac, txl, k - 1), gidx(bp, txp, k));
-    }
-    __syncthreads();
-
-    // Every node of the group now points at its group root in the forest, and
-    // the border slots that k_seam reads (the group's outer rows and columns,
-    // and the end pixels of tile rows at the group's left and right columns)
-    // name that group root directly.
-    for (int li = tid; li < BN; li += NTB) {
-        const int ti = li / NSLOTS, sl = li % NSLOTS;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int w = w0 + k * (NTB / 64), ti = w / SPANS, sl = (w % SPANS) * 64 + lane;
+        if (!inside(ti)) continue;
         const int txl = ti % BX, tyl = ti / BX;
-        const int tx = tx0 + txl, ty = ty0 + tyl;
-        if (tx >= a.ntx || ty >= a.nty) continue;
-        const int64_t base = (a.tbase + (int64_t)ty * a.ntx + tx) * NSLOTS;
-        auto node_of = [&](uint32_t l) {
-            const int tj = (int)(l / NSLOTS);
-            return (uint32_t)((a.tbase + (int64_t)(ty0 + tj / BX) * a.ntx + tx0 + tj % BX) *
-                                  NSLOTS +
-                              (int)(l % NSLOTS));
-        };
-        if ((isrep[li >> 5] >> (li & 31)) & 1u) {
-            const uint32_t r = pfind(P, (uint32_t)li);
-            const uint32_t rk = pk_key(r);
-            const uint32_t gkey =
-                (uint32_t)((int64_t)(py0 + (int)(rk / BPX)) * a.W + px0 + (int)(rk % BPX));
-            ws.forest[base + sl] = ((uint64_t)gkey << 32) | node_of(pk_id(r));
-        }
-        const int32_t node = S[li];
-        if (node < 0) continue;
+        const bool rep = gi[k] == w * 64 + lane;
         const bool top = sl < TW, bot = sl >= TW && sl < 2 * TW;
         const int xs = sl % TW;
         const bool outer = (top && tyl == 0) || (bot && tyl == BY - 1) ||
                            (sl >= 2 * TW && sl < 2 * TW + TILE_ROWS && txl == 0) ||
                            (sl >= 2 * TW + TILE_ROWS && txl == BX - 1) ||
                            ((top || bot) && ((xs == 0 && txl == 0) || (xs == TW - 1 && txl == BX - 1)));
-        if (outer) {
-            const uint32_t r = pfind(P, gidx(node, txl, tyl));
-            ws.slots[base + sl] = (int32_t)node_of(pk_id(r));
+        const uint32_t base = (uint32_t)tile_of(ti) * NSLOTS;
+        int32_t node = gi[k] < 0 ? -1 : (int32_t)base + (gi[k] - ti * NSLOTS);
+        uint64_t entry = 0ull;
+        if (rep || (outer && gi[k] >= 0)) {
+            const uint32_t r = pfind(P, (uint32_t)gi[k]), root = node_of(pk_id(r)), rk = pk_key(r);
+            if (rep)
+                entry = ((uint64_t)(uint32_t)((int64_t)(py0 + (int)(rk / BPX)) * a.W + px0 +
+                                              (int)(rk % BPX))
+                         << 32) |
+                        root;
+            if (outer) node = (int32_t)root;
         }
+        ws.slots[(int64_t)base + sl] = node;
+        ws.forest[(int64_t)base + sl] = entry;
     }
 }
 
@@ -1963,17 +1966,18 @@ __global__ __launch_bounds__(NT) void k_local_ablate(BatchArgs b, Workspace ws, 
     __syncthreads();
     const int64_t sbase = T * NSLOTS;
     {
-        int32_t node = -1;
+        const bool nodes = b.ngroups == 0;
+        int32_t ent = -1;
         if (fg) {
             const int rep = NSLOTS - 1 - (int)pk_id(lds_ld(sh.P + root));
-            node = (int32_t)(sbase + rep);
-            if (rep == s) {
+            ent = nodes ? (int32_t)sbase + rep : slot_entry(rkey, (uint32_t)rep);
+            if (nodes && rep == s) {
                 const uint32_t gkey = (uint32_t)((int64_t)(gy0 + (int)(rkey / TW)) * a.W +
                                                  gx0 + (int)(rkey % TW));
-                ws.forest[node] = ((uint64_t)gkey << 32) | (uint32_t)node;
+                ws.forest[ent] = ((uint64_t)gkey << 32) | (uint32_t)ent;
             }
         }
-        ws.slots[sbase + s] = node;
+        ws.slots[sbase + s] = ent;
     }
     // run table over row runs: the entry of the node holding each run's first pixel
     uint16_t* rtab = ws.runtab + T * RUNTAB_PER_TILE;
