@@ -242,7 +242,8 @@ static ImageArgs make_args(const uint8_t* img, int32_t H, int32_t W, int64_t pit
     a.W = W;
     a.ntx = (int32_t)(((int64_t)W + TW - 1) / TW);
     a.nty = (int32_t)(((int64_t)H + rows - 1) / rows);
-    a.unused[0] = a.unused[1] = 0;
+    a.unused = 0;
+    a.stream = 0;
     a.wmagic = W == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint64_t)W);
     a.lbase = 0;
     a.tbase = 0;
@@ -317,6 +318,15 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
 // group keep k_block, which is all their merge and leaves their forest flat.
 constexpr int64_t DIRECT_TILES = 512;
 
+// Launches whose label maps exceed this write them around the caches (images
+// whose rows are whole 128-byte lines): the maps would push what the next
+// kernels read out of the 256 MB of cache, and are not there when a consumer
+// reads them either.  Below it the consumer gains from the cached map.  Labels
+// alone, and labels with a maximum taken over them afterwards, cached and
+// around: 4096^2 (67 MB) 54.6 and 75.4 us, 52.6 and 80.1; 5792^2 (134 MB) 88.0
+// and 134.4, 85.5 and 129.4; 8192^2 145 and 244, 132 and 215.
+constexpr int64_t STREAM_BYTES = int64_t(128) << 20;
+
 // Sizes of one connectivity class of a batch.
 struct ClassLayout {
     int n = 0;
@@ -337,14 +347,17 @@ static int layout_class(std::vector<ImageArgs>& imgs, int conn, const ShapeOps& 
     L.toff.assign(n + 1, 0);
     L.goff.assign(n + 1, 0);
     L.soff.assign(n + 1, 0);
-    int64_t tiles = 0, seams = 0;
+    int64_t tiles = 0, seams = 0, px = 0;
     for (const ImageArgs& a : imgs) {
+        px += (int64_t)a.H * a.W;
         tiles += (int64_t)a.ntx * a.nty;
         seams += ops.image_seam_items(a.ntx, a.nty, a.H, a.W, conn, false);
     }
     L.direct = seams > 0 && tiles <= DIRECT_TILES;
+    const bool stream = 4 * px >= STREAM_BYTES;
     for (int i = 0; i < n; ++i) {
         ImageArgs& a = imgs[i];
+        a.stream = stream && (uintptr_t)a.labels % 128 == 0 && a.W % 32 == 0;
         a.tbase = L.toff[i];
         L.toff[i + 1] = L.toff[i] + (int64_t)a.ntx * a.nty;
         L.goff[i + 1] = L.goff[i] + ops.image_groups(a.ntx, a.nty, L.direct);

@@ -37,7 +37,8 @@ struct ImageArgs {
     int32_t ntx, nty;  // tile grid
     uint32_t wmagic;   // floor(2^32 / W) (0xffffffff for W = 1), for division by W
     int32_t lbase;     // added to every label written (a slice's first voxel position)
-    int32_t unused[2];  // keeps the layout at 64 bytes
+    int32_t unused;    // keeps the layout at 64 bytes
+    int32_t stream;    // labels are written around the caches (rows are whole 128-byte lines)
     int64_t tbase;     // global index of the image's first tile in the workspace
 };
 // 64 bytes: the kernels read an image's entry with one scalar load.

@@ -264,6 +264,23 @@ __device__ __forceinline__ void st_labels4(int32_t* p, int32_t a, int32_t b, int
     v.w = (uint32_t)d;
     st_global(reinterpret_cast<v4u32u*>(p), v);
 }
+// The same around the caches, for rows that are whole 128-byte lines (8192^2
+// Bernoulli 0.6: k_final 74 -> 59 us; on rows of other widths the half-written
+// lines cost more than the cache: 256 mixed images 117 -> 184).
+__device__ __forceinline__ void st_labels4_nt(int32_t* p, int32_t a, int32_t b, int32_t c,
+                                              int32_t d)
+{
+    v4u32 v;
+    v.x = (uint32_t)a;
+    v.y = (uint32_t)b;
+    v.z = (uint32_t)c;
+    v.w = (uint32_t)d;
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) v4u32*)p);
+#else
+    *reinterpret_cast<v4u32*>(p) = v;  // host pass: never executed
+#endif
+}
 // The first n of them (n may be negative): the end of a row cut by the edge.
 __device__ __forceinline__ void st_labels(int32_t* p, const int32_t* o, int n)
 {
@@ -513,7 +530,8 @@ __device__ __forceinline__ ImageArgs batch_image(const BatchArgs& b, int i)
     r.nty = p->nty;
     r.wmagic = p->wmagic;
     r.lbase = p->lbase;
-    r.unused[0] = r.unused[1] = 0;
+    r.unused = 0;
+    r.stream = p->stream;
     r.tbase = p->tbase;
     return r;
 }
@@ -1356,7 +1374,9 @@ __device__ void final_tile(const BatchArgs& b, const Workspace& ws, const StatsW
             // a foreground pixel has its run start at or left of it, so cnt >= 1
             o[k] = ((m4 >> k) & 1u) ? sh.lab[cnt ? cnt - 1 : 0] : 0;
         }
-        st_labels(a.labels + (int64_t)gy * a.W + gx0 + x0, o, xmax - x0);
+        int32_t* dst = a.labels + (int64_t)gy * a.W + gx0 + x0;
+        if (a.stream && xmax >= TW) st_labels4_nt(dst, o[0], o[1], o[2], o[3]);
+        else st_labels(dst, o, xmax - x0);
     }
 }
 
@@ -2581,9 +2601,9 @@ __global__ __launch_bounds__(VNT) void k_vfinal(VolArgs v)
 // byte of bits and row bases plus two bytes per run each way, where the
 // in-place path above writes, reads and rewrites the whole label map.  512^3
 // blobs at 26-connectivity: 748 us in place (local 271, merge 268, relabel
-// 196), 239 here (78, 64, 96; the bytes alone take 118 at the copy rate);
-// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 128 (73, 26, 28).
-// The local step is bound by instruction issue (63 of its 78 us), the merge
+// 196), 230 here (74, 62, 95; the bytes alone take 118 at the copy rate);
+// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 105 (55, 23, 28).
+// The local step is bound by instruction issue (59 of its 74 us), the merge
 // by device-scope atomics on the forest and the loads that lead to them, the
 // relabel by its stores (5.6 TB/s).
 //
@@ -2690,8 +2710,11 @@ __device__ void wbuild_lines(WLines<C>& sh, int tid)
 
 template <int C>
 struct WLocalShared : WLines<C> {
-    uint32_t P[WGeo<C>::MAXR];  // parent of each run, packed (brick key << 16) | id
-    uint32_t ncomp;             // nodes handed out
+    // parent of each run, packed (brick key << 16) | id; behind the brick's
+    // runs, its edges (run | earlier run << 16)
+    uint32_t P[WGeo<C>::MAXR];
+    uint32_t ncomp;   // nodes handed out
+    uint32_t nedges;  // edges found so far
 };
 
 // Edges between the runs of two lines through facing rows T (this line) and
@@ -2738,6 +2761,9 @@ __device__ __forceinline__ uint64_t wface(const uint64_t* M, int l, int dz, int 
 // work by columns where runs are listed and by neighbour line where edges
 // are (group 0 the line above, 1 the line below, 2 and 3 the diagonal lines
 // below): each group computes the edge masks of its own line pair only.
+// Edges are listed behind the runs and merged from there, every lane with
+// work (walked and merged line by line: 201 x 301 x 333 Bernoulli 0.4 at 6
+// 73 us, now 55; 512^3 blobs at 26 79, now 74).
 template <int C>
 __global__ __launch_bounds__(WGeo<C>::NT) void k_wlocal(VolArgs v, VolWs ws)
 {
@@ -2746,23 +2772,24 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wlocal(VolArgs v, VolWs ws)
     const int tid = threadIdx.x;
     const WBrick bk = wbrick_of(v, blockIdx.x);
     {  // sixteen voxels per chunk, four chunks per row; all loads first
-        constexpr int PER = WB_ROWS * 4 / G::NT;
+        constexpr int PER = WB_ROWS * 4 / G::NT, ZSTEP = G::NT / (4 * WB_H);
+        const int x = bk.x0 + 16 * (tid & 3), y = bk.y0 + (tid >> 2) % WB_H;
+        const int z = bk.z0 + tid / (4 * WB_H);
+        const uint8_t* src = v.vol + (int64_t)z * v.spitch + (int64_t)y * v.pitch + x;
+        const uint32_t n = (uint32_t)(v.W - x < 16 ? v.W - x : 16);
+        const bool live = y < v.H && x < v.W;
         Chunk k[PER];
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            const int c = tid + q * G::NT, r = c >> 2;
-            const int x = bk.x0 + 16 * (c & 3), y = bk.y0 + r % WB_H, z = bk.z0 + r / WB_H;
             k[q].lo = k[q].hi = make_uint4(0u, 0u, 0u, 0u);
             k[q].off = k[q].n = 0u;
-            if (z < v.D && y < v.H && x < v.W)
-                k[q] = fetch_segment(v.vol + (int64_t)z * v.spitch + (int64_t)y * v.pitch + x,
-                                     (uint32_t)(v.W - x < 16 ? v.W - x : 16));
+            if (live && z + q * ZSTEP < v.D) k[q] = fetch_segment(src + q * ZSTEP * v.spitch, n);
         }
         uint16_t* h = reinterpret_cast<uint16_t*>(sh.M);
 #pragma unroll
         for (int q = 0; q < PER; ++q) h[tid + q * G::NT] = (uint16_t)chunk_mask(k[q]);
     }
-    if (tid == 0) sh.ncomp = 0u;
+    if (tid == 0) sh.ncomp = sh.nedges = 0u;
     __syncthreads();
     const int64_t b = blockIdx.x;
     if (tid < WB_ROWS) ws.bits[b * WB_ROWS + tid] = sh.M[tid];
@@ -2812,78 +2839,110 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wlocal(VolArgs v, VolWs ws)
         B = C == 26 ? wface(sh.M, nl, -dz, -dy) : nm;
     }
     WEdges e = wedges<C>(T, B);
-    __syncthreads();
-    // Coarse links: a run takes the entry of the run its first edge to the
-    // line above leads to (group 0) or, if it has none, its first edge to the
-    // line below (group 1): plain stores, one writer per run.  The entry
-    // taken must have a smaller key than the run: always so for the line
-    // below and for rows, while a bundle's run may start before the run of
-    // the bundle above that it touches (that edge is merged later).
-    if (g <= 1) {
-        const uint64_t low = e.e0 | e.e2 | (e.e1 >> 1);  // this line's voxel of each edge
-        uint64_t f = first_in_run(lm, ls, low);
-        if (g == 1 && ly > 0) {
-            // leave out the runs that have an edge to the line above
-            const uint64_t U = C == 26 ? wface(sh.M, l - 1, 0, 1) : sh.M[l - 1];
-            const uint64_t Ty = C == 26 ? wface(sh.M, l, 0, -1) : lm;
-            const WEdges ey = wedges<C>(Ty, U);
-            const uint64_t lowy = ey.e0 | ey.e2 | (ey.e1 >> 1);
-            uint64_t keep = 0;
-            for (uint64_t w = f; w; w &= w - 1ull) {
-                const int p = ctz64(w);
-                const int s0 = msb64(ls & upto(p));
-                const uint64_t span = lm & ~(lm + (1ull << s0)) & (~0ull << s0);
-                if (!(lowy & span)) keep |= 1ull << p;
-            }
-            f = keep;
-        }
-        for (uint64_t w = f; w; w &= w - 1ull) {
-            const int p = ctz64(w);
-            const uint64_t pb = 1ull << p;
-            // upper column: p, p - 1 (e2) or p + 1 (e1)
-            const int u = (e.e0 & pb) ? p : (e.e2 & pb) ? p - 1 : p + 1;
-            uint32_t* mine = sh.P + (lbase + popc64(ls & upto(p)));
-            const uint32_t up = lds_ld(sh.P + (nbase + popc64(ns & upto(u))));
-            if (C == 26 && up > lds_ld(mine)) continue;
-            lds_st(mine, up);
-            // the link's own edge needs no merge
-            if (e.e0 & pb) e.e0 &= ~pb;
-            else if (e.e2 & pb) e.e2 &= ~pb;
-            else e.e1 &= ~(pb << 1);
-        }
+    const uint64_t low = e.e0 | e.e2 | (e.e1 >> 1);  // this line's voxel of each edge
+    // Coarse links, of groups 0 and 1: a run's first edge to the line above
+    // or, if it has none there, its first edge to the line below.
+    uint64_t f = g <= 1 ? first_in_run(lm, ls, low) : 0ull;
+    if (g == 1 && ly > 0) {
+        const uint64_t U = C == 26 ? wface(sh.M, l - 1, 0, 1) : sh.M[l - 1];
+        const uint64_t Ty = C == 26 ? wface(sh.M, l, 0, -1) : lm;
+        const WEdges ey = wedges<C>(Ty, U);
+        const uint64_t fy = first_in_run(lm, ls, ey.e0 | ey.e2 | (ey.e1 >> 1));
+        // the columns of runs with an edge above: a carry from that edge runs
+        // to the run's end, and with the bits reversed to its start
+        const uint64_t rl = __builtin_bitreverse64(lm), rf = __builtin_bitreverse64(fy);
+        f &= ~(lm ^ (lm + fy)) & ~__builtin_bitreverse64(rl ^ (rl + rf));
     }
     __syncthreads();
-    for (uint32_t id = tid; id < R; id += G::NT)
-        __hip_atomic_fetch_min(sh.P + id, pfind(sh.P, id), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    __syncthreads();
-    // Refinement: the remaining edges, in two 32-column halves.  An edge
-    // whose two runs' current parents are the pair this thread merged last,
-    // or are one run, is dropped.
-    {
-        uint32_t last = ~0u;
-        uint32_t pl = lbase, pn = nbase;  // runs left of the half, less one
+    // Columns are walked in two 32-bit halves: fn(bit, bits at or left of it,
+    // runs of this line and of the neighbour starting there, those of the
+    // neighbour one column further, runs left of the half).
+    auto halves = [&](uint64_t cols, auto&& fn) {
+        uint32_t pl = lbase, pn = nbase;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t e1 = (uint32_t)(e.e1 >> (32 * h)), e2 = (uint32_t)(e.e2 >> (32 * h));
             const uint32_t sl = (uint32_t)(ls >> (32 * h)), sn = (uint32_t)(ns >> (32 * h));
-            for (uint32_t w = (uint32_t)(e.e0 >> (32 * h)) | e1 | e2; w; w &= w - 1u) {
-                const uint32_t bit = w & (0u - w), upto_i = bit | (bit - 1u), left = bit - 1u;
-                // runs starting at or left of the edge's columns: i, or i - 1
-                // on this line for e1, on the other for e2
-                const uint32_t x = pl + __builtin_popcount(sl & (e1 & bit ? left : upto_i));
-                const uint32_t y = pn + __builtin_popcount(sn & (e2 & bit ? left : upto_i));
-                const uint32_t pa = pk_id(lds_ld(sh.P + x)), pb = pk_id(lds_ld(sh.P + y));
-                if (pa == pb) continue;
-                const uint32_t pair = (pa << 16) | pb;
-                if (pair == last) continue;
-                last = pair;
-                punion(sh.P, x, y);
+            const uint32_t sx = (uint32_t)(ns >> (32 * h) >> 1);
+            for (uint32_t w = (uint32_t)(cols >> (32 * h)); w; w &= w - 1u) {
+                const uint32_t bit = w & (0u - w);
+                fn(h, bit, bit | (bit - 1u), sl, sn, sx, pl, pn);
             }
             pl += __builtin_popcount(sl);
             pn += __builtin_popcount(sn);
         }
+    };
+    // A link takes the entry of the run above or below (plain stores, one
+    // writer per run), which must have a smaller key than the run: always so
+    // for the line below and for rows, while a bundle's run may start before
+    // the run of the bundle above that it touches (that edge is merged later).
+    if (f) {
+        uint32_t linked[2] = {0u, 0u};
+        halves(f, [&](int h, uint32_t bit, uint32_t upto_i, uint32_t sl, uint32_t sn, uint32_t sx,
+                      uint32_t pl, uint32_t pn) {
+            uint32_t y = pn + __builtin_popcount(sn & upto_i);
+            if (C == 26 && !((uint32_t)(e.e0 >> (32 * h)) & bit)) {
+                // the neighbour's column is one left (e2) or one right (e1)
+                if ((uint32_t)(e.e2 >> (32 * h)) & bit) y -= (sn & bit) ? 1u : 0u;
+                else y += (sx & bit) ? 1u : 0u;
+            }
+            uint32_t* mine = sh.P + (pl + __builtin_popcount(sl & upto_i));
+            const uint32_t up = lds_ld(sh.P + y);
+            if (C == 26 && up > lds_ld(mine)) return;
+            lds_st(mine, up);
+            linked[h] |= bit;
+        });
+        // a link's own edge needs no merge
+        const uint64_t lk = linked[0] | ((uint64_t)linked[1] << 32);
+        e.e1 &= ~((lk & ~e.e0 & ~e.e2) << 1);
+        e.e0 &= ~lk;
+        e.e2 &= ~lk;
     }
+    // The other edges are listed behind the runs in P, so that every lane has
+    // work when they are merged; a thread whose edges do not fit keeps them,
+    // and voids the entries it was given.
+    uint32_t* EL = sh.P + R;
+    const uint32_t cap = (uint32_t)G::MAXR - R;
+    uint64_t rest = e.e0 | e.e1 | e.e2;
+    auto edge_at = [&](int h, uint32_t bit, uint32_t upto_i, uint32_t sl, uint32_t sn, uint32_t pl,
+                       uint32_t pn, uint32_t& x, uint32_t& y) {
+        // runs at column i, or i - 1 on this line for e1, on the other for e2
+        const uint32_t left = bit - 1u;
+        x = pl + __builtin_popcount(sl & ((uint32_t)(e.e1 >> (32 * h)) & bit ? left : upto_i));
+        y = pn + __builtin_popcount(sn & ((uint32_t)(e.e2 >> (32 * h)) & bit ? left : upto_i));
+    };
+    if (rest) {
+        const uint32_t n = popc64(rest);
+        uint32_t off = atomicAdd(&sh.nedges, n);
+        if (off + n <= cap) {
+            halves(rest, [&](int h, uint32_t bit, uint32_t upto_i, uint32_t sl, uint32_t sn,
+                             uint32_t, uint32_t pl, uint32_t pn) {
+                uint32_t x, y;
+                edge_at(h, bit, upto_i, sl, sn, pl, pn, x, y);
+                EL[off++] = x | (y << 16);
+            });
+            rest = 0ull;
+        } else {
+            for (; off < cap; ++off) EL[off] = 0u;  // run 0 with itself
+        }
+    }
+    __syncthreads();
+    const uint32_t E = min(sh.nedges, cap);
+    // Unification (an atomic min: a merge may already have linked the run),
+    // then the merges (Section 3.1.3).
+    for (uint32_t id = tid; id < R; id += G::NT)
+        __hip_atomic_fetch_min(sh.P + id, pfind(sh.P, id), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (uint32_t i = tid; i < E; i += G::NT) {
+        const uint32_t ed = EL[i];
+        punion(sh.P, ed & 0xffffu, ed >> 16);
+    }
+    if (rest)
+        halves(rest, [&](int h, uint32_t bit, uint32_t upto_i, uint32_t sl, uint32_t sn, uint32_t,
+                         uint32_t pl, uint32_t pn) {
+            uint32_t x, y;
+            edge_at(h, bit, upto_i, sl, sn, pl, pn, x, y);
+            punion(sh.P, x, y);
+        });
     __syncthreads();
     for (uint32_t id = tid; id < R; id += G::NT) lds_st(sh.P + id, pfind(sh.P, id));
     __syncthreads();
@@ -2953,8 +3012,13 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wlocal(VolArgs v, VolWs ws)
 //       above it in the slab, within the slab (26: likewise along z and x);
 //   x face: voxels of column x0 against column x0-1 of the left brick within
 //       the slab and row band.
-// As in the local step an edge stands for a stretch of touching voxels.  A
-// workgroup drops pairs it has already taken (LDS hash).
+// As in the local step an edge stands for a stretch of touching voxels.  The
+// pairs of components go into an LDS hash, which drops duplicates, and are
+// united from there, those across one face before the diagonal ones: most of
+// these then meet at once (64.4 -> 62.6 us on 512^3 blobs at 26, 26.0 -> 22.9 on
+// 201 x 301 x 333 Bernoulli 0.4 at 6, against uniting every pair where it was
+// found).  Bound half by the loads that lead to the pairs (34 us of the 62
+// without any union), half by device-scope atomics.
 constexpr int WM_NT = 256;
 constexpr int WM_HASH = 512;
 template <int C>
@@ -2991,23 +3055,35 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
         uint32_t h = key * 0x9e3779b1u >> 16;
         for (int probe = 0; probe < 8; ++probe, ++h) {
             const uint32_t old = atomicCAS(seen + (h & (WM_HASH - 1)), ~0u, key);
-            if (old == key) return;
-            if (old == ~0u) break;
+            if (old == key || old == ~0u) return;
         }
         g_union(ws.forest, (uint32_t)b * G::CAP + na, (uint32_t)bb * G::CAP + nb);
     };
     static_assert(G::CAP <= 4096, "component numbers fit 12 bits of the hash key");
+    // unites the pairs of the hash: all (pass 0), those across one face (1),
+    // the others (2)
+    auto drain = [&](int pass) {
+        for (int i = tid; i < WM_HASH; i += WM_NT) {
+            const uint32_t key = seen[i];
+            if (key == ~0u) continue;
+            const int c = (int)((key >> 12) & 31u);
+            const bool face = c == 4 || c == 10 || c == 12;  // one step along z, y or x
+            if (pass && face != (pass == 1)) continue;
+            const int64_t bb = b + (c / 9 - 1) * dz1 + (c / 3 % 3 - 1) * dy1 + (c % 3 - 1);
+            g_union(ws.forest, (uint32_t)b * G::CAP + (key >> 17), (uint32_t)bb * G::CAP + (key & 0xfffu));
+        }
+    };
     auto code_of = [](int dz, int dy, int dx) { return (dz + 1) * 9 + (dy + 1) * 3 + dx + 1; };
 
     // line la of this brick (facing rows T) against line lb of brick bb
     // (facing rows B): edges whose index lies in columns c0 .. c0+15
     auto rows = [&](int la, uint64_t lma, uint64_t T, int64_t bb, int code, int lb, uint64_t lmb,
                     uint64_t B, int c0) {
+        const uint32_t ba = ws.base[b * G::BSTRIDE + la], bbase = ws.base[bb * G::BSTRIDE + lb];
         const WEdges e = wedges<C>(T, B);
         uint64_t w = (e.e0 | e.e1 | e.e2) & (0xffffull << c0);
         if (!w) return;
         const uint64_t lsa = lma & ~(lma << 1), lsb = lmb & ~(lmb << 1);
-        const uint32_t ba = ws.base[b * G::BSTRIDE + la], bbase = ws.base[bb * G::BSTRIDE + lb];
         for (; w; w &= w - 1ull) {
             const int i = ctz64(w);
             const int xa = (e.e1 >> i) & 1ull ? i - 1 : i, xb = (e.e2 >> i) & 1ull ? i - 1 : i;
@@ -3035,6 +3111,8 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
                           number(b - 1, ws.base[(b - 1) * G::BSTRIDE + l + 1] - 1u));
             }
         }
+        __syncthreads();
+        drain(0);
         return;
     }
     constexpr int LH = G::LH;  // 8 x 8 bundles
@@ -3108,6 +3186,10 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
                 }
         }
     }
+    __syncthreads();
+    drain(1);
+    __syncthreads();
+    drain(2);
 }
 
 template <int C>

@@ -38,10 +38,16 @@ def test_edges_of_bricks(ccl, shape, conn):
 
 
 @pytest.mark.parametrize("conn", [6, 26])
-@pytest.mark.parametrize("kind", ["checkerboard", "full", "empty", "lattice", "lattice2", "blobs"])
+@pytest.mark.parametrize("kind", ["checkerboard", "full", "empty", "lattice", "lattice2",
+                                  "dominoes", "blobs"])
 def test_contents(ccl, kind, conn):
     shape = (50, 130, 449)
-    if kind.startswith("lattice"):
+    if kind == "dominoes":
+        # 2 x 2 x 1 pieces: the most runs a bundle of rows can have, and more
+        # edges between bundles than the edge list takes
+        z, y, x = np.indices(shape)
+        vol = ((z // 2 + y // 2 + x) % 2 == 0).astype(np.uint8)
+    elif kind.startswith("lattice"):
         # isolated voxels: the most components a brick can have (26), and a
         # second lattice that joins some of them diagonally
         vol = np.zeros(shape, np.uint8)
