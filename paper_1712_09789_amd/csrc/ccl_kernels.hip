@@ -190,20 +190,32 @@ __device__ void punion_count(uint32_t* P, uint32_t a, uint32_t b, uint32_t& it, 
     }
 }
 
-// The paper's merge (Section 3.1.3): compare the two roots and point the one
-// with the larger key at the other, atomically; if it stopped being a root
-// in the meantime, continue with the parent it had.
+// The paper's merge (Section 3.1.3) without finding both roots: the two paths
+// are climbed together until their parents meet.  Each step lowers the entry
+// on the side whose parent has the larger key to the other side's parent, by
+// an atomic min; if that entry was a root it is now linked, else its old
+// parent is still to be united (Rem's algorithm with splicing).  Entries only
+// decrease, so walks end and the smallest key stays the root.  Against finds
+// with path halving on both sides: k_local on 8192^2 Bernoulli 0.6 96.8 -> 90.1
+// us, on 4096^2 Bernoulli 0.5 30.0 -> 27.9, k_block on 256 mixed images 36.9 ->
+// 31.2, k_wlocal on 201 x 301 x 333 Bernoulli 0.4 54.9 -> 51.5; with plain
+// climbs past non-roots 96.4, 30.2, 35.4 and 58.1.
 __device__ void punion(uint32_t* P, uint32_t a, uint32_t b)
 {
-    while (true) {
-        uint32_t ra = pfind(P, a), rb = pfind(P, b);
-        if (ra == rb) return;
-        if (ra < rb) { uint32_t t = ra; ra = rb; rb = t; }
-        const uint32_t old = __hip_atomic_fetch_min(P + pk_id(ra), rb, __ATOMIC_RELAXED,
+    uint32_t va = lds_ld(P + a), vb = lds_ld(P + b);
+    while (va != vb) {
+        if (va < vb) {
+            const uint32_t t = a, tv = va;
+            a = b;
+            b = t;
+            va = vb;
+            vb = tv;
+        }
+        const uint32_t old = __hip_atomic_fetch_min(P + a, vb, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (old == ra) return;
+        if (pk_id(old) == a) return;
         a = pk_id(old);
-        b = pk_id(rb);
+        va = lds_ld(P + a);
     }
 }
 
@@ -1043,7 +1055,7 @@ constexpr int NTB = 1024;  // threads per merge-group workgroup
 // scalar.  All it reads are the slot tables, whose entries carry the tile key
 // of their component (with the keys in the forest, read besides and divided by
 // the width, and addresses per lane: 24 us on 8192^2 Bernoulli 0.6, 44 on 256
-// mixed images, 10 at 4096^2; now 18, 36 and 8).
+// mixed images, 10 at 4096^2; now 17, 31 and 7).
 template <int D>
 __global__ __launch_bounds__(NTB) void k_block(BatchArgs b, Workspace ws)
 {
@@ -2601,9 +2613,9 @@ __global__ __launch_bounds__(VNT) void k_vfinal(VolArgs v)
 // byte of bits and row bases plus two bytes per run each way, where the
 // in-place path above writes, reads and rewrites the whole label map.  512^3
 // blobs at 26-connectivity: 748 us in place (local 271, merge 268, relabel
-// 196), 230 here (74, 62, 95; the bytes alone take 118 at the copy rate);
-// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 105 (55, 23, 28).
-// The local step is bound by instruction issue (59 of its 74 us), the merge
+// 196), 226 here (70, 62, 95; the bytes alone take 118 at the copy rate);
+// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 102 (51, 23, 28).
+// The local step is bound by instruction issue, the merge
 // by device-scope atomics on the forest and the loads that lead to them, the
 // relabel by its stores (5.6 TB/s).
 //
