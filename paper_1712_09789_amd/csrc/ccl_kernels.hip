@@ -1494,6 +1494,8 @@ __device__ __forceinline__ uint32_t bit_position_sum(uint64_t m)
            16u * popc64(m & 0xFFFF0000FFFF0000ull) + 32u * popc64(m & 0xFFFFFFFF00000000ull);
 }
 
+constexpr uint16_t NO_ROOT = 0xffff;
+
 template <int D>
 struct StatsShared : Lines<D> {
     uint16_t RL[Geo<D>::MAXR];
@@ -1506,6 +1508,7 @@ struct StatsShared : Lines<D> {
     // border components of the tile, by representative slot
     uint64_t sums[NSLOTS], cols[NSLOTS], rows[NSLOTS];
     int32_t lab[NSLOTS];
+    uint16_t rootkey[NSLOTS];  // tile position of its smallest pixel, NO_ROOT if in another tile
     // interior components, at the run holding their smallest pixel
     uint64_t isums[Geo<D>::MAXR], icols[Geo<D>::MAXR], irows[Geo<D>::MAXR];
     uint8_t iroot[Geo<D>::MAXR];
@@ -1558,9 +1561,8 @@ __device__ __forceinline__ int64_t tile_number(const SH& sh, int ky, int kx)
 // components are summed per component in LDS and leave the tile as one
 // partial record each, which k_stats_merge combines over 4 x 4 tiles before
 // they reach the entries, so that a component spanning the image is not
-// updated once per tile.  The run holding a border component's smallest
-// pixel writes the entry's starting values (label, top row, empty sums and
-// box).  Components whose smallest pixel lies in this tile are numbered
+// updated once per tile.  The tile holding a border component's smallest
+// pixel starts its entry with its own part.  Components whose smallest pixel lies in this tile are numbered
 // from the tile's staged row counts; the partial records carry the label.
 // Threads per tile: at 4-connectivity its LDS allows two workgroups per
 // compute unit, and a wide one keeps the unit busy; at 8 it allows four, and
@@ -1590,6 +1592,7 @@ __global__ __launch_bounds__(STATS_T<D>) void k_stats(BatchArgs b, Workspace ws,
     if (tid < NSLOTS) {
         sh.sums[tid] = sh.cols[tid] = sh.rows[tid] = 0ull;
         sh.lab[tid] = st.fin[T * NSLOTS + tid];  // used at representative slots only
+        sh.rootkey[tid] = NO_ROOT;
     }
     // the whole run table, in the same round trip as the loads above (its
     // entries past the tile's run count are never read)
@@ -1663,20 +1666,8 @@ __global__ __launch_bounds__(STATS_T<D>) void k_stats(BatchArgs b, Workspace ws,
             atomicAdd(&sh.sums[rep], packed);
             atomicOr(&sh.cols[rep], colm);
             atomicOr(&sh.rows[rep], rowm);
-            if (!is_root) continue;
+            if (is_root) sh.rootkey[rep] = (uint16_t)key;
         }
-        // the component's entry starts from its label and top row; the
-        // merge adds every tile's part to it
-        const int64_t num = tile_number(sh, (int)(key / TW), (int)(key % TW));
-        if (num >= st.capacity) continue;
-        CompStats c;
-        c.label = L;
-        c.area = 0;
-        c.x_min = INT32_MAX;
-        c.y_min = (int32_t)(kpos / a.W);
-        c.x_max = c.y_max = -1;
-        c.sum_x = c.sum_y = 0;
-        st_global(st.comps + num, c);
     }
     __syncthreads();
     // interior components: the whole entry from the run holding the smallest pixel
@@ -1709,23 +1700,41 @@ __global__ __launch_bounds__(STATS_T<D>) void k_stats(BatchArgs b, Workspace ws,
         c.sum_y = (int64_t)(((v >> 31) & 0x3ffffu) + (uint64_t)area * gy0);
         st_global(st.comps + num, c);
     }
-    // one partial record per border component of the tile
+    // One partial record per border component of the tile.  The tile that holds
+    // its smallest pixel starts the component's entry with its own part, and
+    // marks its record (negative label): a component of two tiles, in two
+    // regions of the merge, then takes one set of atomics, not two.
     const uint64_t v = tid < NSLOTS ? sh.sums[tid] : 0ull;
     const int area = (int)(v & 0x1fffu);
     if (area > 0) {
-        {
-            StatRec r;
-            r.label = sh.lab[tid];
-            r.area = area;
-            const uint64_t cm = sh.cols[tid], rm = sh.rows[tid];
-            r.x_min = gx0 + ctz64(cm);
-            r.x_max = gx0 + msb64(cm);
-            r.y_min = gy0 + ctz64(rm);
-            r.y_max = gy0 + msb64(rm);
-            r.sum_x = (int64_t)(((v >> 13) & 0x3ffffu) + (uint64_t)area * gx0);
-            r.sum_y = (int64_t)(((v >> 31) & 0x3ffffu) + (uint64_t)area * gy0);
-            st.rec0[T * NSLOTS + atomicAdd(&sh.nrec, 1u)] = r;
+        StatRec r;
+        r.label = sh.lab[tid];
+        r.area = area;
+        const uint64_t cm = sh.cols[tid], rm = sh.rows[tid];
+        r.x_min = gx0 + ctz64(cm);
+        r.x_max = gx0 + msb64(cm);
+        r.y_min = gy0 + ctz64(rm);
+        r.y_max = gy0 + msb64(rm);
+        r.sum_x = (int64_t)(((v >> 13) & 0x3ffffu) + (uint64_t)area * gx0);
+        r.sum_y = (int64_t)(((v >> 31) & 0x3ffffu) + (uint64_t)area * gy0);
+        const uint32_t key = sh.rootkey[tid];
+        if (key != NO_ROOT) {
+            const int64_t num = tile_number(sh, (int)(key / TW), (int)(key % TW));
+            if (num < st.capacity) {
+                CompStats c;
+                c.label = r.label;
+                c.area = area;
+                c.x_min = r.x_min;
+                c.y_min = gy0 + (int)(key / TW);
+                c.x_max = r.x_max;
+                c.y_max = r.y_max;
+                c.sum_x = r.sum_x;
+                c.sum_y = r.sum_y;
+                st_global(st.comps + num, c);
+            }
+            r.label = -r.label;
         }
+        st.rec0[T * NSLOTS + atomicAdd(&sh.nrec, 1u)] = r;
     }
     __syncthreads();
     if (tid == 0) st.cnt0[T] = sh.nrec;
@@ -1738,12 +1747,15 @@ __global__ __launch_bounds__(STATS_T<D>) void k_stats(BatchArgs b, Workspace ws,
 // per tile).  A combined record whose box stays off the region's
 // inner edges (image edges do not count) is the whole component: it cannot
 // reach outside without crossing them, so its fields are stored into the
-// component's entry (started by the tile holding its smallest pixel, which
-// wrote the label and top row).  The others are added to the entry with
-// atomics, where a component's parts from several regions meet.  Records
-// that find the table full go straight to the entries with atomics; then
-// the workgroup stores nothing plainly, since a store could hide them.
+// component's entry (started by the tile holding its smallest pixel).  The
+// others are added to the entry with atomics, where a component's parts from
+// several regions meet, less the part the entry was started with.  Bound by
+// those device-scope atomics, six per part (4096^2 Bernoulli 0.3, 8-connected:
+// 16.8 us with entries started empty and every region's part added, 12.0 so).
+// Records that find the table full go straight to the entries with atomics;
+// then the workgroup stores nothing plainly, since a store could hide them.
 constexpr int MERGE_T = 1024;
+static_assert(MERGE_FAN * MERGE_FAN * NSLOTS <= 0x8000, "16-bit record numbers");
 __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatRec* in,
                                                           const uint32_t* in_cnt, int in_cap,
                                                           int inx, int iny, int outx,
@@ -1753,6 +1765,7 @@ __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatR
     __shared__ int32_t hkey[MERGE_HT], harea[MERGE_HT], hxmin[MERGE_HT], hxmax[MERGE_HT],
         hymin[MERGE_HT], hymax[MERGE_HT];
     __shared__ unsigned long long hsx[MERGE_HT], hsy[MERGE_HT];
+    __shared__ int16_t hown[MERGE_HT];  // record of the tile that started the entry, -1 = elsewhere
     __shared__ int overflow;
     const int tid = threadIdx.x;
     for (int h = tid; h < MERGE_HT; h += MERGE_T) {
@@ -1761,6 +1774,7 @@ __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatR
         hxmin[h] = hymin[h] = INT32_MAX;
         hxmax[h] = hymax[h] = -1;
         hsx[h] = hsy[h] = 0ull;
+        hown[h] = -1;
     }
     if (tid == 0) overflow = 0;
     __syncthreads();
@@ -1785,12 +1799,14 @@ __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatR
         for (int q = 0; q < RPT; ++q) {
             if (k0 + pl + q * TPP >= n) continue;
             const StatRec& r = rec[q];
-            uint32_t h = ((uint32_t)r.label * 0x9E3779B1u) >> (32 - 11);
+            const bool own = r.label < 0;
+            const int32_t label = own ? -r.label : r.label;
+            uint32_t h = ((uint32_t)label * 0x9E3779B1u) >> (32 - 11);
             static_assert(MERGE_HT == 1 << 11, "hash width");
             bool placed = false;
             for (int probe = 0; probe < 64 && !placed; ++probe, h = (h + 1u) & (MERGE_HT - 1)) {
-                const int32_t old = atomicCAS(&hkey[h], -1, r.label);
-                if (old == -1 || old == r.label) {
+                const int32_t old = atomicCAS(&hkey[h], -1, label);
+                if (old == -1 || old == label) {
                     atomicAdd(&harea[h], r.area);
                     atomicMin(&hxmin[h], r.x_min);
                     atomicMax(&hxmax[h], r.x_max);
@@ -1798,13 +1814,14 @@ __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatR
                     atomicMax(&hymax[h], r.y_max);
                     atomicAdd(&hsx[h], (unsigned long long)r.sum_x);
                     atomicAdd(&hsy[h], (unsigned long long)r.sum_y);
+                    if (own) hown[h] = (int16_t)(part * NSLOTS + k0 + pl + q * TPP);
                     placed = true;
                 }
             }
             if (!placed) {
                 overflow = 1;
-                const int64_t num = component_number(a, st, r.label);
-                if (num < st.capacity)
+                const int64_t num = component_number(a, st, label);
+                if (num < st.capacity && !own)
                     add_stats(st.comps + num, r.area, r.x_min, r.x_max, r.y_max,
                               (uint64_t)r.sum_x, (uint64_t)r.sum_y);
             }
@@ -1825,7 +1842,18 @@ __global__ __launch_bounds__(MERGE_T) void k_stats_merge(StatsWs st, const StatR
                              (hymin[h] == y0 && y0 > 0) || (hymax[h] == y1 && y1 < H - 1);
         CompStats* c = st.comps + num;
         if (crosses || !plain_ok) {
-            add_stats(c, harea[h], hxmin[h], hxmax[h], hymax[h], hsx[h], hsy[h]);
+            int area = harea[h];
+            uint64_t sx = hsx[h], sy = hsy[h];
+            if (hown[h] >= 0) {  // what the entry started with
+                const int op = hown[h] / NSLOTS, ok = hown[h] % NSLOTS;
+                const int64_t og = (int64_t)(J * MERGE_FAN + op / MERGE_FAN) * inx + I * MERGE_FAN +
+                                   op % MERGE_FAN;
+                const StatRec r = ld_global(in + og * in_cap + ok);
+                area -= r.area;
+                sx -= (uint64_t)r.sum_x;
+                sy -= (uint64_t)r.sum_y;
+            }
+            if (area > 0) add_stats(c, area, hxmin[h], hxmax[h], hymax[h], sx, sy);
         } else {
             st_global(&c->area, harea[h]);
             st_global(&c->x_min, hxmin[h]);
@@ -2614,7 +2642,7 @@ __global__ __launch_bounds__(VNT) void k_vfinal(VolArgs v)
 // in-place path above writes, reads and rewrites the whole label map.  512^3
 // blobs at 26-connectivity: 748 us in place (local 271, merge 268, relabel
 // 196), 226 here (70, 62, 95; the bytes alone take 118 at the copy rate);
-// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 102 (51, 23, 28).
+// 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 97 (51, 23, 23).
 // The local step is bound by instruction issue, the merge
 // by device-scope atomics on the forest and the loads that lead to them, the
 // relabel by its stores (5.6 TB/s).
@@ -2653,6 +2681,16 @@ __device__ __forceinline__ WBrick wbrick_of(const VolArgs& v, uint32_t i)
     k.y0 = (int)(r / (uint32_t)v.wnbx) * WB_H;
     k.z0 = (int)bz * WB_D;
     return k;
+}
+
+// Workgroups are dealt to the eight XCDs in turn.  The relabel takes its bricks
+// in runs of XCD_RUN neighbours per XCD, so that the cache line where the rows
+// of two bricks meet is mostly completed in one L2 (201 x 301 x 333: k_wfinal
+// 27.7 -> 23.1 us, runs of four 24.9; volumes of whole lines: no difference).
+constexpr uint32_t XCD_RUN = 16, XCD_SPAN = 8 * XCD_RUN;
+__device__ __forceinline__ uint32_t xcd_brick(uint32_t i)
+{
+    return (i & ~(XCD_SPAN - 1u)) + (i & 7u) * XCD_RUN + ((i >> 3) & (XCD_RUN - 1u));
 }
 
 // First brick row of bundle l (26): rows wrow(l) + {0, 1, WB_H, WB_H + 1}.
@@ -3219,8 +3257,10 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wfinal(VolArgs v, VolWs ws)
     using G = WGeo<C>;
     __shared__ WFinalShared<C> sh;
     const int tid = threadIdx.x;
-    const int64_t b = blockIdx.x;
-    const WBrick bk = wbrick_of(v, blockIdx.x);
+    const uint32_t brick = xcd_brick(blockIdx.x);
+    if (brick >= (uint32_t)(v.wnbx * v.wnby * v.wnbz)) return;
+    const int64_t b = brick;
+    const WBrick bk = wbrick_of(v, brick);
     const int64_t S = (int64_t)v.H * v.W;
     const uint32_t R = ws.base[b * G::BSTRIDE + G::NL];
     const uint32_t nc = ws.ncomp[b];
@@ -3542,8 +3582,9 @@ hipError_t launch_volume_ws(const VolArgs& v, const VolWs& ws, int conn, hipStre
         timer_end(timer, KIND_VMERGE, st);
     }
     timer_begin(timer, KIND_VFINAL, st);
-    if (conn == 26) k_wfinal<26><<<g, WGeo<26>::NT, 0, st>>>(v, ws);
-    else k_wfinal<6><<<g, WGeo<6>::NT, 0, st>>>(v, ws);
+    const unsigned gx = (g + XCD_SPAN - 1) / XCD_SPAN * XCD_SPAN;
+    if (conn == 26) k_wfinal<26><<<gx, WGeo<26>::NT, 0, st>>>(v, ws);
+    else k_wfinal<6><<<gx, WGeo<6>::NT, 0, st>>>(v, ws);
     timer_end(timer, KIND_VFINAL, st);
     return hipGetLastError();
 }
