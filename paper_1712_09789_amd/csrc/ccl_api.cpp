@@ -773,6 +773,8 @@ int ccl_label_3d(const uint8_t* vol, int32_t D, int32_t H, int32_t W, int64_t pi
     v.wnbx = (int32_t)(((int64_t)W + VOL_WS_W - 1) / VOL_WS_W);
     v.wnby = (int32_t)(((int64_t)H + VOL_WS_H - 1) / VOL_WS_H);
     v.wnbz = (int32_t)(((int64_t)D + VOL_WS_D - 1) / VOL_WS_D);
+    v.wslab_magic = magic((int64_t)v.wnbx * v.wnby);
+    v.wrow_magic = magic(v.wnbx);
     VolWs vws;
     hipError_t e = volume_workspace(v, connectivity, st, &vws)
                        ? r64::launch_volume_ws(v, vws, connectivity, st, active_timer())

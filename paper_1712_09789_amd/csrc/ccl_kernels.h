@@ -56,6 +56,7 @@ struct VolArgs {
     int32_t vec;            // labels is 16-byte aligned
     uint32_t wmagic, smagic;  // floor(2^32 / W), floor(2^32 / (H * W)); 0xffffffff for 1
     int32_t wnbx, wnby, wnbz;  // bricks of the workspace path
+    uint32_t wslab_magic, wrow_magic;  // for division by wnbx * wnby and wnbx
 };
 constexpr int VOL_BRICK_W = 64, VOL_BRICK_H = 8, VOL_BRICK_D = 8;  // voxels per brick (x, y, z)
 

@@ -2641,7 +2641,7 @@ __global__ __launch_bounds__(VNT) void k_vfinal(VolArgs v)
 // byte of bits and row bases plus two bytes per run each way, where the
 // in-place path above writes, reads and rewrites the whole label map.  512^3
 // blobs at 26-connectivity: 748 us in place (local 271, merge 268, relabel
-// 196), 226 here (70, 62, 95; the bytes alone take 118 at the copy rate);
+// 196), 215 here (69, 51, 95; the bytes alone take 118 at the copy rate);
 // 201 x 301 x 333 Bernoulli 0.4 at 6: 208 (72, 70, 68) and 97 (51, 23, 23).
 // The local step is bound by instruction issue, the merge
 // by device-scope atomics on the forest and the loads that lead to them, the
@@ -2674,13 +2674,11 @@ struct WBrick {
 };
 __device__ __forceinline__ WBrick wbrick_of(const VolArgs& v, uint32_t i)
 {
-    WBrick k;
-    const uint32_t per_slab = (uint32_t)v.wnbx * (uint32_t)v.wnby;
-    const uint32_t bz = i / per_slab, r = i - bz * per_slab;
-    k.x0 = (int)(r % (uint32_t)v.wnbx) * WB_W;
-    k.y0 = (int)(r / (uint32_t)v.wnbx) * WB_H;
-    k.z0 = (int)bz * WB_D;
-    return k;
+    // i is a workgroup's: the multiplications run on the scalar unit
+    uint32_t bz, by, bx, r;
+    divmod_w(i, (uint32_t)v.wnbx * (uint32_t)v.wnby, v.wslab_magic, bz, r);
+    divmod_w(r, (uint32_t)v.wnbx, v.wrow_magic, by, bx);
+    return WBrick{(int)bx * WB_W, (int)by * WB_H, (int)bz * WB_D};
 }
 
 // Workgroups are dealt to the eight XCDs in turn.  The relabel takes its bricks
@@ -3068,13 +3066,31 @@ __global__ __launch_bounds__(WGeo<C>::NT) void k_wlocal(VolArgs v, VolWs ws)
 // these then meet at once (64.4 -> 62.6 us on 512^3 blobs at 26, 26.0 -> 22.9 on
 // 201 x 301 x 333 Bernoulli 0.4 at 6, against uniting every pair where it was
 // found).  Bound half by the loads that lead to the pairs (34 us of the 62
-// without any union), half by device-scope atomics.
-constexpr int WM_NT = 256;
-constexpr int WM_HASH = 512;
+// without any union, with 16 columns), half by device-scope atomics.
+//
+// Each thread takes WIN columns of a pair of rows.  Wide windows load a row pair
+// once instead of four times, narrow ones give the serial walk over the edges to
+// more threads: while all workgroups are resident at once the latency of that
+// walk is what counts, beyond that the instructions.  Hence 26-connectivity
+// takes 16 columns while the grid of those fits the card and whole rows from
+// there on, volumes at Bernoulli 0.1 / 0.2 / blobs of radius 2, us with 16 and 64:
+// 201 x 301 x 333 (1482 bricks) 82 / 85 / 61 and 88 / 93 / 64, 320^3 (2000) 104 /
+// 102 / 74 and 110 / 110 / 77; 352^3 (2904) 129 / 140 / 95 and 129 / 137 / 92,
+// 512^3 (8192) 318 / 332 / 225 and 309 / 329 / 215 (this kernel there: 62 and 51).
+// At 6-connectivity 32 columns gained nothing at any size.
 template <int C>
-__global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
+constexpr int WM_PAIRS = C == 26 ? 2 * 3 * (WB_H / 2) : 2 * WB_H;
+// threads of the row pairs, in whole wavefronts: the x face's come after them
+template <int C, int WIN>
+constexpr int WM_X0 = (WM_PAIRS<C> * (WB_W / WIN) + 63) / 64 * 64;
+template <int C, int WIN>
+constexpr int WM_NT = WM_X0<C, WIN> + (C == 26 ? 64 : 128);
+constexpr int WM_HASH = 512;
+template <int C, int WIN>
+__global__ __launch_bounds__((WM_NT<C, WIN>)) void k_wmerge(VolArgs v, VolWs ws)
 {
     using G = WGeo<C>;
+    constexpr int NT = WM_NT<C, WIN>, WPR = WB_W / WIN;
     __shared__ uint32_t seen[WM_HASH];
     __shared__ uint64_t col0[WB_ROWS / 64], col63[WB_ROWS / 64];  // x-face voxels by row
     const int tid = threadIdx.x;
@@ -3082,14 +3098,16 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
     const WBrick bk = wbrick_of(v, blockIdx.x);
     const int64_t dy1 = v.wnbx, dz1 = (int64_t)v.wnbx * v.wnby;
     const bool hasx = bk.x0 > 0, hasy = bk.y0 > 0, hasz = bk.z0 > 0;
-    for (int i = tid; i < WM_HASH; i += WM_NT) seen[i] = ~0u;
+    for (int i = tid; i < WM_HASH; i += NT) seen[i] = ~0u;
     if (C == 26) {
-        const uint64_t a = hasx ? ws.bits[b * WB_ROWS + tid] : 0ull;
-        const uint64_t c = hasx ? ws.bits[(b - 1) * WB_ROWS + tid] : 0ull;
-        const uint64_t ma = __ballot(a & 1ull), mc = __ballot(c >> 63);
-        if ((tid & 63) == 0) {
-            col0[tid >> 6] = ma;
-            col63[tid >> 6] = mc;
+        for (int r = tid; r < WB_ROWS; r += NT) {  // whole wavefronts
+            const uint64_t a = hasx ? ws.bits[b * WB_ROWS + r] : 0ull;
+            const uint64_t c = hasx ? ws.bits[(b - 1) * WB_ROWS + r] : 0ull;
+            const uint64_t ma = __ballot(a & 1ull), mc = __ballot(c >> 63);
+            if ((r & 63) == 0) {
+                col0[r >> 6] = ma;
+                col63[r >> 6] = mc;
+            }
         }
     }
     __syncthreads();
@@ -3113,7 +3131,7 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
     // unites the pairs of the hash: all (pass 0), those across one face (1),
     // the others (2)
     auto drain = [&](int pass) {
-        for (int i = tid; i < WM_HASH; i += WM_NT) {
+        for (int i = tid; i < WM_HASH; i += NT) {
             const uint32_t key = seen[i];
             if (key == ~0u) continue;
             const int c = (int)((key >> 12) & 31u);
@@ -3126,12 +3144,12 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
     auto code_of = [](int dz, int dy, int dx) { return (dz + 1) * 9 + (dy + 1) * 3 + dx + 1; };
 
     // line la of this brick (facing rows T) against line lb of brick bb
-    // (facing rows B): edges whose index lies in columns c0 .. c0+15
+    // (facing rows B): edges whose index lies in columns c0 .. c0 + WIN - 1
     auto rows = [&](int la, uint64_t lma, uint64_t T, int64_t bb, int code, int lb, uint64_t lmb,
                     uint64_t B, int c0) {
         const uint32_t ba = ws.base[b * G::BSTRIDE + la], bbase = ws.base[bb * G::BSTRIDE + lb];
         const WEdges e = wedges<C>(T, B);
-        uint64_t w = (e.e0 | e.e1 | e.e2) & (0xffffull << c0);
+        uint64_t w = (e.e0 | e.e1 | e.e2) & ((WIN == 64 ? ~0ull : (1ull << (WIN & 63)) - 1ull) << c0);
         if (!w) return;
         const uint64_t lsa = lma & ~(lma << 1), lsb = lmb & ~(lmb << 1);
         for (; w; w &= w - 1ull) {
@@ -3142,8 +3160,8 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
         }
     };
     if (C == 6) {
-        if (tid < 8 * WB_H) {
-            const int t = tid >> 2, c0 = (tid & 3) * 16;
+        if (tid < WM_PAIRS<C> * WPR) {
+            const int t = tid / WPR, c0 = (tid % WPR) * WIN;
             const bool zf = t < WB_H;
             const int k = zf ? t : t - WB_H;
             if (zf ? hasz : hasy) {
@@ -3153,8 +3171,8 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
                 const uint64_t A = ws.bits[b * WB_ROWS + la], B = ws.bits[bb * WB_ROWS + lb];
                 rows(la, A, A, bb, zf ? code_of(-1, 0, 0) : code_of(0, -1, 0), lb, B, B, c0);
             }
-        } else if (hasx) {
-            for (int l = tid - 8 * WB_H; l < WB_ROWS; l += WM_NT - 8 * WB_H) {
+        } else if (tid >= WM_X0<C, WIN> && hasx) {
+            for (int l = tid - WM_X0<C, WIN>; l < WB_ROWS; l += NT - WM_X0<C, WIN>) {
                 const uint64_t A = ws.bits[b * WB_ROWS + l], B = ws.bits[(b - 1) * WB_ROWS + l];
                 if ((A & 1ull) && (B >> 63))
                     unite(number(b, ws.base[b * G::BSTRIDE + l]), b - 1, code_of(0, 0, -1),
@@ -3167,8 +3185,8 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
     }
     constexpr int LH = G::LH;  // 8 x 8 bundles
     const bool hasyh = bk.y0 + WB_H < v.H, hasxh = bk.x0 + WB_W < v.W;
-    if (tid < 2 * 3 * LH * 4) {
-        const int t = tid >> 2, c0 = (tid & 3) * 16;
+    if (tid < WM_PAIRS<C> * WPR) {
+        const int t = tid / WPR, c0 = (tid % WPR) * WIN;
         const bool zf = t < 3 * LH;
         const int k = (zf ? t : t - 3 * LH) / 3, d = (zf ? t : t - 3 * LH) % 3 - 1;
         int k2 = k + d, sy = 0;  // the neighbour's line and its brick's step along y
@@ -3203,14 +3221,14 @@ __global__ __launch_bounds__(WM_NT) void k_wmerge(VolArgs v, VolWs ws)
             if (c0 == 0 && hasx && (T & 1ull) && (wface(MB - WB_ROWS, lb, -dz, -dy) >> 63))
                 unite(number(b, ws.base[b * G::BSTRIDE + la]), bb - 1, code_of(bz, sy, -1),
                       number(bb - 1, ws.base[(bb - 1) * G::BSTRIDE + lb + 1] - 1u));
-            if (c0 == 48 && hasxh && (T >> 63) && (wface(MB + WB_ROWS, lb, -dz, -dy) & 1ull))
+            if (c0 == WB_W - WIN && hasxh && (T >> 63) && (wface(MB + WB_ROWS, lb, -dz, -dy) & 1ull))
                 unite(number(b, ws.base[b * G::BSTRIDE + la + 1] - 1u), bb + 1,
                       code_of(bz, sy, 1), number(bb + 1, ws.base[(bb + 1) * G::BSTRIDE + lb]));
         }
-    } else if (hasx) {
+    } else if (tid >= WM_X0<C, WIN> && hasx) {
         // x face: bundle i of this brick against the 3 x 3 bundles around it
         // in the left brick
-        const int i = tid - 2 * 3 * LH * 4, by = i % LH, bz = i / LH;
+        const int i = tid - WM_X0<C, WIN>, by = i % LH, bz = i / LH;
         // bit k: row k of the bundle ((0,0), (0,1), (1,0), (1,1) along z, y)
         auto four = [&](const uint64_t* col, int l) {
             const int r = wrow(l);
@@ -3577,8 +3595,11 @@ hipError_t launch_volume_ws(const VolArgs& v, const VolWs& ws, int conn, hipStre
     timer_end(timer, KIND_VLOCAL, st);
     if (g > 1) {
         timer_begin(timer, KIND_VMERGE, st);
-        if (conn == 26) k_wmerge<26><<<g, WM_NT, 0, st>>>(v, ws);
-        else k_wmerge<6><<<g, WM_NT, 0, st>>>(v, ws);
+        constexpr int NT26 = WM_NT<26, 16>;
+        if (conn != 26) k_wmerge<6, 16><<<g, WM_NT<6, 16>, 0, st>>>(v, ws);
+        else if (g <= resident_blocks(k_wmerge<26, 16>, NT26))
+            k_wmerge<26, 16><<<g, NT26, 0, st>>>(v, ws);
+        else k_wmerge<26, 64><<<g, WM_NT<26, 64>, 0, st>>>(v, ws);
         timer_end(timer, KIND_VMERGE, st);
     }
     timer_begin(timer, KIND_VFINAL, st);

@@ -60,6 +60,14 @@ def test_contents(ccl, kind, conn):
     check(ccl, vol, conn)
 
 
+# more bricks than fit the card at once, along y and z and with ends of rows in
+# two bricks each
+@pytest.mark.parametrize("conn", [6, 26])
+@pytest.mark.parametrize("shape", [(737, 721, 3), (8209, 17, 65)])
+def test_many_bricks(ccl, shape, conn):
+    check(ccl, wl.bernoulli3d(*shape, 0.13 if conn == 26 else 0.35, seed=9), conn)
+
+
 @pytest.mark.parametrize("conn", [6, 26])
 def test_pitched_view_and_unaligned_labels(ccl, conn):
     big = wl.bernoulli3d(60, 150, 460, 0.3, seed=4) * np.uint8(200)
