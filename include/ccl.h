@@ -187,11 +187,11 @@ int ccl_label_stats(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  * (runs along x united across the brick's rows and slices), components are
  * united across brick faces in the label map (the block merge), and every
  * label is rewritten to its root.  Volumes of at least 192 bricks of 64 x 16
- * x 16 voxels (or of one) are labelled through the stream's cached workspace
- * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks), which
- * writes each label once; smaller volumes, single slices, calls on a stream
- * that is being captured and calls whose workspace cannot be had need no
- * workspace.  The labels are the same.
+ * x 16 voxels (or of one) are labelled through a workspace, which writes each
+ * label once: a cached buffer of the stream's apart from that of image calls
+ * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks).
+ * Smaller volumes, single slices, calls on a stream that is being captured
+ * and calls whose workspace cannot be had need none.  The labels are the same.
  *   vol           device, uint8, D slices of H rows; row y of slice z starts
  *                 at vol + z * slice_pitch_bytes + y * pitch_bytes;
  *                 caller-owned, only read.
@@ -290,8 +290,8 @@ int32_t ccl_tile_rows(void);
    sizes). */
 int64_t ccl_workspace_bytes(int32_t H, int32_t W);
 
-/* Bytes of the workspace the library currently keeps for `stream` on the
-   current device (0 if none): it grows to 1.25 x the largest need seen on
+/* Bytes of the workspace the library currently keeps for image calls on
+   `stream` of the current device (0 if none): it grows to 1.25 x the largest need seen on
    that stream and is kept until ccl_release_workspace.  For callers that
    account device memory (a serving loop's admission). */
 int64_t ccl_workspace_cached(void* stream);

@@ -10,6 +10,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -35,6 +36,10 @@ static int fail(int status, const char* fmt, ...)
 // ---------------------------------------------------------------------------
 // workspace cache: one grow-only buffer per (device, stream)
 // ---------------------------------------------------------------------------
+//
+// Volumes have a buffer of their own: a graph captured from image calls, and
+// ccl_replay_last, go on using the stream's image buffer, which a volume must
+// therefore neither overwrite nor free in order to grow.
 
 struct WsEntry {
     void* ptr = nullptr;
@@ -42,15 +47,16 @@ struct WsEntry {
 };
 
 static std::mutex g_ws_mu;
-static std::map<std::pair<int, hipStream_t>, WsEntry> g_ws;
+enum WsKind { WS_IMAGES, WS_VOLUMES };
+static std::map<std::tuple<int, hipStream_t, WsKind>, WsEntry> g_ws;
 
-static int get_workspace(int64_t need, hipStream_t st, void** out)
+static int get_workspace(int64_t need, hipStream_t st, void** out, WsKind kind = WS_IMAGES)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    WsEntry& w = g_ws[{dev, st}];
+    WsEntry& w = g_ws[{dev, st, kind}];
     if (w.bytes < need) {
         if (w.ptr) {
             // earlier work on this stream may still read the old buffer
@@ -524,8 +530,14 @@ static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* 
         return false;
     }
     if (cap != hipStreamCaptureStatusNone) return false;
+    // growing the workspace must not spoil a capture that another thread has
+    // under way on a stream of its own
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void* base = nullptr;
-    if (get_workspace(vol_workspace(nullptr, nb, conn, nullptr), st, &base) != CCL_OK) {
+    const int rc = get_workspace(vol_workspace(nullptr, nb, conn, nullptr), st, &base, WS_VOLUMES);
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (rc != CCL_OK) {
         g_err.clear();
         return false;
     }
@@ -979,7 +991,7 @@ int64_t ccl_workspace_cached(void* stream)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    const auto it = g_ws.find({dev, static_cast<hipStream_t>(stream)});
+    const auto it = g_ws.find({dev, static_cast<hipStream_t>(stream), WS_IMAGES});
     return it == g_ws.end() ? 0 : it->second.bytes;
 }
 
@@ -994,7 +1006,7 @@ int ccl_release_workspace(int32_t device)
     std::lock_guard<std::mutex> lk(g_ws_mu);
     bool any = false;
     for (auto it = g_ws.begin(); it != g_ws.end();) {
-        if (it->first.first == device) {
+        if (std::get<0>(it->first) == device) {
             if (!any) {
                 if ((e = hipSetDevice(device)) != hipSuccess)
                     return fail(CCL_ERR_HIP, "hipSetDevice: %s", hipGetErrorString(e));

@@ -98,3 +98,31 @@ def test_capture_replays_in_place(ccl, conn):
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), want[k])
+
+
+def test_volumes_leave_the_image_workspace_alone(ccl):
+    """A graph captured from an image call keeps its workspace when a volume
+    that needs a larger one is labelled on the same stream."""
+    from oracle import oracle_label
+    img = wl.bernoulli(300, 500, 0.55, seed=1)
+    vol = wl.bernoulli3d(100, 200, 400, 0.3, seed=2)
+    d, dv = torch.from_numpy(img).cuda(), torch.from_numpy(vol).cuda()
+    out = torch.zeros(img.shape, dtype=torch.int32, device="cuda")
+    outv = torch.zeros(vol.shape, dtype=torch.int32, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        ccl.label(d, 8, out=out)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            ccl.label(d, 8, out=out)
+        held = ccl.workspace_cached(s)
+        for conn in (6, 26):
+            ccl.label_3d(dv, conn, out=outv)
+            assert ccl.workspace_cached(s) == held
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert np.array_equal(out.cpu().numpy(), oracle_label(img, 8))
+            assert np.array_equal(outv.cpu().numpy(), oracle_label3d(vol, conn))
