@@ -186,12 +186,13 @@ int ccl_label_stats(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  * a third axis: bricks of 64 x 8 x 8 voxels (x, y, z) are labelled in LDS
  * (runs along x united across the brick's rows and slices), components are
  * united across brick faces in the label map (the block merge), and every
- * label is rewritten to its root.  Volumes of at least 192 bricks of 64 x 16
- * x 16 voxels (or of one) are labelled through a workspace, which writes each
- * label once: a cached buffer of the stream's apart from that of image calls
+ * label is rewritten to its root.  Volumes of 32 rows or more are labelled
+ * through a workspace, in bricks of 64 x 16 x 16 voxels, and each label is
+ * written once: a cached buffer of the stream's apart from that of image calls
  * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks).
- * Smaller volumes, single slices, calls on a stream that is being captured
- * and calls whose workspace cannot be had need none.  The labels are the same.
+ * Smaller volumes, thin ones whose whole bricks would take over 150 MB, calls
+ * on a stream that is being captured and calls whose workspace cannot be had
+ * need none.  The labels are the same.
  *   vol           device, uint8, D slices of H rows; row y of slice z starts
  *                 at vol + z * slice_pitch_bytes + y * pitch_bytes;
  *                 caller-owned, only read.

@@ -507,10 +507,13 @@ static int label_one(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, in
 
 // Workspace of a volume, or false where it is labelled in place, which needs
 // none:
-//  * fewer than 192 bricks of 64 x 16 x 16 (but more than one), or one slice:
-//    the in-place path's bricks are a quarter of that and fill the chip
-//    sooner (100^3, 98 bricks: 55 us in place, 58 here; 129^3, 243 bricks: 67
-//    and 60; 512^3: 730 and 250);
+//  * fewer than 32 rows: a brick here has 256 rows and its fixed cost shows
+//    (1 x 1 x 5000 voxels: 13.5 us in place, 16.7 here; 2 x 8 x 64: 9-22 and
+//    11).  From there on this path wins at every size; in place and here, us at
+//    6 / 26 neighbours on Bernoulli 0.35 / 0.2: 7 x 7 x 50 11.8 / 16.6 and 11.7
+//    / 14.7, 1 x 512 x 512 20 / 25 and 19 / 22, 33 x 40 x 43 43 / 44 and 31 / 35,
+//    64^3 45 / 46 and 37 / 47, 128^3 57 / 58 and 41 / 50, 150^3 78 / 70 and 47 /
+//    54, 2 x 1000 x 1000 37 / 57 and 31 / 36; 512^3 blobs at 26: 739 and 214;
 //  * thin volumes whose workspace would be large (over 150 MB with bricks less
 //    than a third full; at a full 64 x 16 x 16 it is 2.3 bytes per voxel);
 //  * a workspace that cannot be had, and calls on a stream that is being
@@ -520,7 +523,7 @@ static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* 
 {
     const int64_t nb = (int64_t)v.wnbx * v.wnby * v.wnbz;
     const int64_t n = (int64_t)v.D * v.H * v.W;
-    if (v.D < 2 || (nb > 1 && nb < 192) || (int64_t)v.nbx * v.nby * v.nbz == 1 ||
+    if ((int64_t)v.D * v.H < 32 ||
         (nb > 4096 && nb * (VOL_WS_W * VOL_WS_H * VOL_WS_D) > 3 * n) ||
         nb * vol_ws_nodes(conn) > (int64_t)INT32_MAX)
         return false;

@@ -1,6 +1,5 @@
-"""Volumes of at least 192 bricks of 64 x 16 x 16 voxels, or of one such
-brick, which take the workspace path of ccl_label_3d, against the 3-D oracle
-(tolerance 0)."""
+"""The workspace path of ccl_label_3d (volumes of 32 rows or more) and the
+rules beside it, against the 3-D oracle (tolerance 0)."""
 import numpy as np
 import pytest
 
@@ -27,10 +26,12 @@ def check(ccl, vol, conn, view=None, out=None):
     assert np.array_equal(got.cpu().numpy(), oracle_label3d(vol, conn))
 
 
-# one brick; then at least 192 with remainders 1, 15, 16 along y and z and
-# 1, 63, 64 columns along x
+# both sides of the line at 32 rows; one brick; then remainders 1, 15, 16 along
+# y and z and 1, 63, 64 columns along x
 @pytest.mark.parametrize("conn", [6, 26])
-@pytest.mark.parametrize("shape", [(2, 9, 5), (16, 16, 64), (15, 16, 63), (49, 64, 705),
+@pytest.mark.parametrize("shape", [(1, 31, 130), (1, 32, 130), (31, 1, 65), (32, 1, 65),
+                                   (2, 16, 129), (3, 11, 1), (8, 8, 64), (17, 17, 65),
+                                   (2, 9, 5), (16, 16, 64), (15, 16, 63), (49, 64, 705),
                                    (63, 65, 640), (48, 79, 767), (64, 256, 192)])
 def test_edges_of_bricks(ccl, shape, conn):
     for p in (0.15, 0.35, 0.6):
@@ -78,10 +79,11 @@ def test_pitched_view_and_unaligned_labels(ccl, conn):
 
 
 @pytest.mark.parametrize("conn", [6, 26])
-def test_capture_replays_in_place(ccl, conn):
+@pytest.mark.parametrize("shape", [(64, 256, 192), (33, 41, 131)])
+def test_capture_replays_in_place(ccl, shape, conn):
     """Under capture the call labels in place (nothing is allocated, and the
     graph holds no pointer into this stream's workspace)."""
-    vol = wl.bernoulli3d(64, 256, 192, 0.3, seed=6)
+    vol = wl.bernoulli3d(*shape, 0.3, seed=6)
     d = torch.from_numpy(vol).cuda()
     out = torch.zeros(vol.shape, dtype=torch.int32, device="cuda")
     want = [oracle_label3d(v, conn) for v in (vol, 1 - vol)]
