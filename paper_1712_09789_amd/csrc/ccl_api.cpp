@@ -333,12 +333,27 @@ constexpr int64_t DIRECT_TILES = 512;
 // and 134.4, 85.5 and 129.4; 8192^2 145 and 244, 132 and 215.
 constexpr int64_t STREAM_BYTES = int64_t(128) << 20;
 
+// Single images whose label map outgrows the cache and has rows that are not
+// whole 128-byte lines relabel neighbouring tiles on the same XCD, in pairs: the
+// line where the rows of two tiles meet is then written to memory once, not once
+// per part.  8190 x 8195 Bernoulli 0.4 at 4- and 8-connectivity 191 and 209 us in
+// plain order, 182 and 198 in pairs; 17001 x 17003 828 and 820, 714 and 755.
+// Below, the parts meet in the cache, and what is left (6001^2 98 and 107, 96 and
+// 105) is less than chains of one component lose, whose paths are shortened by
+// the tiles in their order (500 x 777 serpentine 24 to 31); at 8190 x 8195 that
+// order costs them nothing (178 and 204, 177 and 202).  Runs of four gain more
+// on noise (177 and 193) and lose there (179 and 204; 11000 x 11003 serpentine
+// 327 and 346, pairs 328 and 350, fours 346 and 373).  Of batches, noise gains 6 %
+// and spirals lose 3 %.
+constexpr int64_t PAIR_BYTES = int64_t(256) << 20;
+
 // Sizes of one connectivity class of a batch.
 struct ClassLayout {
     int n = 0;
     int rows = DEFAULT_ROWS;
     std::vector<int64_t> toff, goff, soff;  // prefix offsets (n+1 each)
     int64_t ntiles = 0, ngroups = 0, nseamwg = 0;
+    bool paired = false;  // the relabel takes neighbouring tiles in pairs per XCD
     bool direct = false;  // tiles merged across every seam at once, no groups
     int64_t head = 0;  // bytes of the device tables (0 for a single image)
     int64_t bytes() const { return head + workspace_bytes(ntiles, rows); }
@@ -363,7 +378,9 @@ static int layout_class(std::vector<ImageArgs>& imgs, int conn, const ShapeOps& 
     const bool stream = 4 * px >= STREAM_BYTES;
     for (int i = 0; i < n; ++i) {
         ImageArgs& a = imgs[i];
-        a.stream = stream && (uintptr_t)a.labels % 128 == 0 && a.W % 32 == 0;
+        const bool whole = (uintptr_t)a.labels % 128 == 0 && a.W % 32 == 0;
+        a.stream = stream && whole;
+        L.paired = n == 1 && !whole && 4 * px >= PAIR_BYTES;
         a.tbase = L.toff[i];
         L.toff[i + 1] = L.toff[i] + (int64_t)a.ntx * a.nty;
         L.goff[i + 1] = L.goff[i] + ops.image_groups(a.ntx, a.nty, L.direct);
@@ -393,6 +410,7 @@ static int bind_class(const std::vector<ImageArgs>& imgs, const ClassLayout& L, 
     b = BatchArgs{};
     b.n = n;
     b.direct = L.direct;
+    b.paired = L.paired;
     b.ntiles = L.ntiles;
     b.ngroups = local_only ? 0 : L.ngroups;
     b.nseamwg = local_only ? 0 : L.nseamwg;

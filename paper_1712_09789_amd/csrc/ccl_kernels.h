@@ -120,6 +120,7 @@ struct BatchArgs {
     int32_t n;
     int32_t direct;  // no merge groups: k_seam unites the tiles across every seam
     int64_t ntiles, ngroups, nseamwg;
+    int32_t paired;  // k_final takes neighbouring tiles in pairs per XCD
 };
 
 // Device workspace of one image.

@@ -1392,21 +1392,32 @@ __device__ void final_tile(const BatchArgs& b, const Workspace& ws, const StatsW
     }
 }
 
-// Persistent over tiles like k_local: each workgroup takes tiles blockIdx.x,
-// + gridDim.x, ... and issues the next tile's loads before labelling the
-// current one.
-template <int D, bool LOCAL_ONLY, bool STATS>
+// Tile i of the paired order: workgroups are dealt to the eight XCDs in turn, so
+// i and i + 8 run on one XCD and take neighbouring tiles (in whole spans of
+// sixteen; a grid that is a multiple of eight keeps a workgroup on its XCD).
+__device__ __forceinline__ int64_t paired_tile(int64_t i, int64_t ntiles)
+{
+    if (i >= (ntiles & ~int64_t(15))) return i;
+    const uint32_t r = (uint32_t)i & 15u;
+    return i - r + (r & 7u) * 2 + (r >> 3);
+}
+
+// Persistent over tiles: each workgroup takes tiles blockIdx.x, + gridDim.x,
+// ... (of the paired order with PAIRED) and issues the next tile's loads before
+// labelling the current one.
+template <int D, bool LOCAL_ONLY, bool STATS, bool PAIRED = false>
 __global__ __launch_bounds__(NT) void k_final(BatchArgs b, Workspace ws, StatsWs st)
 {
     __shared__ FinalShared<D> sh;
     const int tid = threadIdx.x;
-    int64_t T = blockIdx.x;
-    if (T >= b.ntiles) return;
-    FinalFetch next = final_fetch(ws, T, tid);
-    for (; T < b.ntiles; T += gridDim.x) {
+    int64_t i = blockIdx.x;
+    if (i >= b.ntiles) return;
+    auto tile = [&](int64_t j) { return PAIRED ? paired_tile(j, b.ntiles) : j; };
+    FinalFetch next = final_fetch(ws, tile(i), tid);
+    for (; i < b.ntiles; i += gridDim.x) {
         const FinalFetch cur = next;
-        if (T + gridDim.x < b.ntiles) next = final_fetch(ws, T + gridDim.x, tid);
-        final_tile<D, LOCAL_ONLY, STATS>(b, ws, st, sh, T, cur, tid);
+        if (i + gridDim.x < b.ntiles) next = final_fetch(ws, tile(i + gridDim.x), tid);
+        final_tile<D, LOCAL_ONLY, STATS>(b, ws, st, sh, tile(i), cur, tid);
         __syncthreads();
     }
 }
@@ -3422,6 +3433,15 @@ static unsigned final_grid(const BatchArgs& b, unsigned resident, GridChoice g)
     return g.final_ == 1 ? (unsigned)b.ntiles : (unsigned)std::min<int64_t>(b.ntiles, resident);
 }
 
+// Launches k_final without statistics.
+template <int D>
+static void launch_final(const BatchArgs& b, const Workspace& ws, hipStream_t st, GridChoice g)
+{
+    const unsigned grid = final_grid(b, resident_blocks(k_final<D, false, false>, NT), g);
+    if (b.paired) k_final<D, false, false, true><<<grid, NT, 0, st>>>(b, ws, StatsWs{});
+    else k_final<D, false, false><<<grid, NT, 0, st>>>(b, ws, StatsWs{});
+}
+
 // Launches k_local with the split for few tiles or, beyond the workgroups of
 // that split that the device holds at once, the one for many.
 template <int D>
@@ -3482,9 +3502,8 @@ static hipError_t launch_all(const BatchArgs& b, const Workspace& ws, hipStream_
         timer_end(timer, KIND_SEAM, st);
     }
     if (!stats) {
-        const unsigned fgrid = final_grid(b, resident_blocks(k_final<D, false, false>, NT), grid);
         timer_begin(timer, KIND_FINAL, st);
-        k_final<D, false, false><<<fgrid, NT, 0, st>>>(b, ws, none);
+        launch_final<D>(b, ws, st, grid);
         timer_end(timer, KIND_FINAL, st);
         return hipGetLastError();
     }
@@ -3532,8 +3551,7 @@ static hipError_t replay_all(const BatchArgs& b, const Workspace& ws, hipStream_
     if (kind == KIND_LOCAL) {
         for (int r = 0; r < reps; ++r) launch_local<D>(b, ws, st);
     } else if (kind == KIND_FINAL) {
-        const unsigned g = final_grid(b, resident_blocks(k_final<D, false, false>, NT), grid);
-        for (int r = 0; r < reps; ++r) k_final<D, false, false><<<g, NT, 0, st>>>(b, ws, StatsWs{});
+        for (int r = 0; r < reps; ++r) launch_final<D>(b, ws, st, grid);
     } else {
         return hipErrorInvalidValue;
     }

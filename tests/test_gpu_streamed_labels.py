@@ -37,6 +37,22 @@ def test_large_maps(ccl, shape, conn):
         flat.fill_(-1)
 
 
+# maps of 256 MiB or more off 128-byte lines: tiles taken in pairs, with a last
+# span of fewer than sixteen; one column less than the line; explicit heights
+@pytest.mark.parametrize("shape,rows", [((8193, 8193), None), ((70, 958_700), None),
+                                        ((8191, 8193), None), ((8193, 8195), 32),
+                                        ((8193, 8195), 64)])
+@pytest.mark.parametrize("conn", [4, 8])
+def test_paired_tiles(ccl, shape, rows, conn):
+    img = wl.bernoulli(*shape, 0.55 if conn == 4 else 0.4, seed=shape[0])
+    d = torch.from_numpy(img).cuda()
+    out = torch.full((img.size + 32,), -1, dtype=torch.int32, device="cuda")
+    got = out[:img.size].view(shape)
+    ccl.label(d, conn, out=got, **({"tile_rows": rows} if rows else {}))
+    assert torch.equal(got, torch.from_numpy(oracle_label(img, conn)).cuda())
+    assert int(out[img.size]) == -1
+
+
 def test_batch_of_both_kinds(ccl):
     imgs = [wl.bernoulli(4000, 4096, 0.4, seed=1), wl.bernoulli(4100, 4001, 0.4, seed=2),
             wl.blobs(700, 96, 4.0, seed=3), wl.full(70, 64)]
