@@ -318,9 +318,9 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
 // (k_block, then k_seam between groups): below it the merge is two launches'
 // latency, above it the longer chains of a forest over all tiles cost more
 // than the launch.  640 x 480 (40 tiles of 128 rows) and 2048^2 (512) blobs,
-// Bernoulli 0.41 and serpentine at 8-connectivity: 18.4, 24.4 and 19.9 us
-// against 22.7, 31.8 and 22.6; 27.5, 41.0, 34.8 against 31.9, 43.7, 31.7;
-// 3000^2 (1128): 39.1, 63.1, 67.6 against 42.4, 61.3, 48.1.  Images of one
+// Bernoulli 0.41 and serpentine at 8-connectivity: 18.3, 24.3 and 21.7 us
+// against 22.9, 27.8 and 22.2; 26.6, 37.6, 34.6 against 29.1, 37.1, 29.5;
+// 3000^2 (1128): 37.6, 54.9, 56.8 against 37.9, 53.2, 44.1.  Images of one
 // group keep k_block, which is all their merge and leaves their forest flat.
 constexpr int64_t DIRECT_TILES = 512;
 
