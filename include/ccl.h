@@ -329,9 +329,12 @@ int ccl_timing_read(double* ms, int64_t* launches, int32_t n);
  *         ccl_timing_enable).
  * The final relabel rewrites the same labels.  The local step resets the
  * block merge's state in the workspace, so after it the labels of that call
- * are valid only once it is made again.  The workspace must not have been
- * used by a larger call on the same stream since.  CCL_ERR_INVALID_ARG for
- * another kind, reps < 0, or no such call.
+ * are valid only once it is made again: a final relabel replayed before that
+ * writes each tile's own labels (as ccl_label_local does), after one further
+ * launch of the local step.  `stream` has to be ordered after that call and
+ * after earlier replays.  The workspace must not have been used by a larger
+ * call on the same stream since.  CCL_ERR_INVALID_ARG for another kind,
+ * reps < 0, or no such call.
  */
 int ccl_replay_last(int32_t kind, int32_t reps, void* stream);
 

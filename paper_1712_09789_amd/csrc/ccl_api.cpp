@@ -467,6 +467,7 @@ struct LastLaunch {
     Choice ch{};
     BatchArgs b{};
     Workspace ws{};
+    bool keyed = false;  // a replayed local step left tile keys in the slots, not forest nodes
 };
 static thread_local LastLaunch g_last;
 
@@ -506,6 +507,7 @@ static int run_batch(std::vector<ImageArgs>& imgs, int conn, const Choice& ch, h
         g_last.ch = ch;
         g_last.b = b;
         g_last.ws = ws;
+        g_last.keyed = false;
     }
     return CCL_OK;
 }
@@ -1110,9 +1112,23 @@ int ccl_replay_last(int32_t kind, int32_t reps, void* stream)
     int dev = -1;
     if (!g_last.valid || hipGetDevice(&dev) != hipSuccess || dev != g_last.device)
         return fail(CCL_ERR_INVALID_ARG, "%s: no labelling call on this thread and device", who);
-    hipError_t e = g_last.ch.ops->replay(g_last.b, g_last.conn, g_last.ws,
-                                         static_cast<hipStream_t>(stream), g_last.ch.grid, kind,
-                                         reps);
+    if (reps == 0) return CCL_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    auto replay = [&](const BatchArgs& b, int k, int n) {
+        return g_last.ch.ops->replay(b, g_last.conn, g_last.ws, st, g_last.ch.grid, k, n);
+    };
+    hipError_t e = hipSuccess;
+    // Where a merge inside groups follows, the local step leaves slot entries
+    // that only this merge turns into the forest nodes the relabel follows: a
+    // relabel replayed after a replayed local step needs the local step of a
+    // launch without groups, which writes nodes and forest itself.
+    if (kind == KIND_FINAL && g_last.keyed) {
+        BatchArgs b = g_last.b;
+        b.ngroups = 0;
+        e = replay(b, KIND_LOCAL, 1);
+    }
+    g_last.keyed = kind == KIND_LOCAL && g_last.b.ngroups > 0;
+    if (e == hipSuccess) e = replay(g_last.b, kind, reps);
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "%s: %s", who, hipGetErrorString(e));
     return CCL_OK;
 }

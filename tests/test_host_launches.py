@@ -1,0 +1,92 @@
+"""What the library's host side allocates, frees, waits for and launches, in
+which order, on the CPU: a child process loads libccl.so over a stand-in for
+the HIP runtime (hip_recorder.cpp) that logs those calls and runs no kernel."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_1712_09789_amd", "libccl.so")
+
+PRELUDE = """
+import collections, ctypes, sys, threading
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+p, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+rec.rec_limit.argtypes = [i64]
+rec.rec_take.argtypes, rec.rec_take.restype = [ctypes.c_char_p, i64], i64
+lib.ccl_label.argtypes = [p, i32, i32, i64, i32, p, p]
+lib.ccl_label_3d.argtypes = [p, i32, i32, i32, i64, i64, i32, p, p]
+lib.ccl_replay_last.argtypes = [i32, i32, p]
+IN, OUT = 1 << 32, 1 << 36
+Event = collections.namedtuple("Event", "what thread ptr value ptr2")
+
+def take():
+    buf = ctypes.create_string_buffer(1 << 22)
+    assert rec.rec_take(buf, len(buf)) < len(buf)
+    rows = [l.split() for l in buf.value.decode().splitlines()]
+    return [Event(w, int(t), int(a, 16), int(v), int(b, 16)) for w, t, a, v, b in rows]
+
+def image(H, W, conn=8, stream=None, at=0):
+    assert lib.ccl_label(IN + at, H, W, W, conn, OUT + 4 * at, stream) == 0
+
+def volume(D, H, W, conn=26, stream=None, at=0):
+    assert lib.ccl_label_3d(IN + at, D, H, W, W, H * W, conn, OUT + 4 * at, stream) == 0
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("rec") / "libhip_recorder.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-w", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "paper_1712_09789_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "hip_recorder.cpp"), "-o", out], check=True)
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code), out, LIB],
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+
+    return run
+
+
+@pytest.mark.parametrize("H,W,grouped", [(4096, 4096, 1), (200, 200, 1), (640, 480, 0), (50, 60, 0)])
+def test_relabel_after_a_replayed_local_step_follows_nodes(recorder, H, W, grouped):
+    # the relabel takes the slots for forest nodes: the launch that wrote them
+    # last has to be a local step without merge groups, or the merge itself
+    recorder(f"""
+        image({H}, {W})
+        first = [e for e in take() if e.what.startswith("launch")]
+        assert any(e.what == "launch:k_block" for e in first) == bool({grouped})
+        for kinds in ((0, 2), (0, 0, 2, 2), (2, 0, 2), (0, 2, 0, 2)):
+            image({H}, {W})
+            for k in kinds:
+                assert lib.ccl_replay_last(k, 2, None) == 0
+        image({H}, {W})
+        lib.ccl_replay_last(2, 1, None)
+        nodes = False
+        for e in take():
+            if e.what == "launch:k_local":
+                nodes = e.value == 0
+            elif e.what == "launch:k_block":
+                nodes = True
+            elif e.what == "launch:k_final":
+                assert nodes
+    """)
+
+
+def test_replays_launch_that_kernel_alone(recorder):
+    recorder("""
+        image(4096, 4096)
+        take()
+        lib.ccl_replay_last(2, 3, None)
+        assert [e.what for e in take()] == ["launch:k_final"] * 3
+        lib.ccl_replay_last(0, 3, None)
+        assert [e.what for e in take()] == ["launch:k_local"] * 3
+        lib.ccl_replay_last(2, 0, None)
+        assert take() == []
+    """)
