@@ -33,7 +33,7 @@
  * The library owns a per-(device, stream) workspace cache that grows on
  * demand (hipMalloc); concurrent calls on DIFFERENT streams use different
  * workspaces and may overlap freely.  Calls on the same stream are ordered
- * by the stream.
+ * by the stream; several threads may make them.
  */
 #ifndef CCL_H
 #define CCL_H

@@ -40,23 +40,37 @@ static int fail(int status, const char* fmt, ...)
 // Volumes have a buffer of their own: a graph captured from image calls, and
 // ccl_replay_last, go on using the stream's image buffer, which a volume must
 // therefore neither overwrite nor free in order to grow.
+//
+// A call holds its buffer's entry from the time it obtains the buffer until its
+// last launch is enqueued: the launches of one call follow each other on the
+// stream, also when several threads use it, and nobody frees or replaces the
+// buffer between them.  Entries are never erased, so that a thread may wait for
+// one.
 
 struct WsEntry {
+    std::mutex mu;
     void* ptr = nullptr;
-    int64_t bytes = 0;
+    std::atomic<int64_t> bytes{0};
 };
+using WsHold = std::unique_lock<std::mutex>;
 
-static std::mutex g_ws_mu;
+static std::mutex g_ws_mu;  // the map; taken before an entry's, never while one is held
 enum WsKind { WS_IMAGES, WS_VOLUMES };
 static std::map<std::tuple<int, hipStream_t, WsKind>, WsEntry> g_ws;
 
-static int get_workspace(int64_t need, hipStream_t st, void** out, WsKind kind = WS_IMAGES)
+static int get_workspace(int64_t need, hipStream_t st, void** out, WsHold& hold,
+                         WsKind kind = WS_IMAGES)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-    std::lock_guard<std::mutex> lk(g_ws_mu);
-    WsEntry& w = g_ws[{dev, st, kind}];
+    WsEntry* entry;
+    {
+        std::lock_guard<std::mutex> lk(g_ws_mu);
+        entry = &g_ws[{dev, st, kind}];
+    }
+    WsEntry& w = *entry;
+    hold = WsHold(w.mu);
     if (w.bytes < need) {
         if (w.ptr) {
             // earlier work on this stream may still read the old buffer
@@ -481,7 +495,8 @@ static int run_batch(std::vector<ImageArgs>& imgs, int conn, const Choice& ch, h
     if (rc != CCL_OK) return rc;
     const int64_t label_bytes = align256(L.bytes());
     void* base = nullptr;
-    rc = get_workspace(label_bytes + (so ? stats_workspace_bytes(L.ntiles) : 0), st, &base);
+    WsHold hold;
+    rc = get_workspace(label_bytes + (so ? stats_workspace_bytes(L.ntiles) : 0), st, &base, hold);
     if (rc != CCL_OK) return rc;
     BatchArgs b;
     Workspace ws;
@@ -539,7 +554,7 @@ static int label_one(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, in
 //  * a workspace that cannot be had, and calls on a stream that is being
 //    captured, where nothing may be allocated and the graph may outlive this
 //    stream's workspace.
-static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* ws)
+static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* ws, WsHold& hold)
 {
     const int64_t nb = (int64_t)v.wnbx * v.wnby * v.wnbz;
     const int64_t n = (int64_t)v.D * v.H * v.W;
@@ -558,7 +573,8 @@ static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* 
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void* base = nullptr;
-    const int rc = get_workspace(vol_workspace(nullptr, nb, conn, nullptr), st, &base, WS_VOLUMES);
+    const int rc =
+        get_workspace(vol_workspace(nullptr, nb, conn, nullptr), st, &base, hold, WS_VOLUMES);
     if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (rc != CCL_OK) {
         g_err.clear();
@@ -811,7 +827,8 @@ int ccl_label_3d(const uint8_t* vol, int32_t D, int32_t H, int32_t W, int64_t pi
     v.wslab_magic = magic((int64_t)v.wnbx * v.wnby);
     v.wrow_magic = magic(v.wnbx);
     VolWs vws;
-    hipError_t e = volume_workspace(v, connectivity, st, &vws)
+    WsHold hold;
+    hipError_t e = volume_workspace(v, connectivity, st, &vws, hold)
                        ? r64::launch_volume_ws(v, vws, connectivity, st, active_timer())
                        : r64::launch_volume(v, connectivity, st, active_timer());
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
@@ -1015,7 +1032,7 @@ int64_t ccl_workspace_cached(void* stream)
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lk(g_ws_mu);
     const auto it = g_ws.find({dev, static_cast<hipStream_t>(stream), WS_IMAGES});
-    return it == g_ws.end() ? 0 : it->second.bytes;
+    return it == g_ws.end() ? 0 : it->second.bytes.load();
 }
 
 const char* ccl_last_error(void) { return g_err.c_str(); }
@@ -1028,18 +1045,24 @@ int ccl_release_workspace(int32_t device)
     if (e != hipSuccess) return fail(CCL_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
     std::lock_guard<std::mutex> lk(g_ws_mu);
     bool any = false;
-    for (auto it = g_ws.begin(); it != g_ws.end();) {
-        if (std::get<0>(it->first) == device) {
-            if (!any) {
-                if ((e = hipSetDevice(device)) != hipSuccess)
-                    return fail(CCL_ERR_HIP, "hipSetDevice: %s", hipGetErrorString(e));
-                (void)hipDeviceSynchronize();
-                any = true;
-            }
-            if (it->second.ptr) (void)hipFree(it->second.ptr);
-            it = g_ws.erase(it);
-        } else {
-            ++it;
+    {
+        // every entry of the device is held before the device is waited for, so
+        // that no call enqueues work on a buffer between the wait and its free
+        std::vector<std::pair<WsEntry*, WsHold>> held;
+        for (auto& kv : g_ws) {
+            if (std::get<0>(kv.first) != device) continue;
+            held.emplace_back(&kv.second, WsHold(kv.second.mu));
+            any = any || kv.second.ptr;
+        }
+        if (any) {
+            if ((e = hipSetDevice(device)) != hipSuccess)
+                return fail(CCL_ERR_HIP, "hipSetDevice: %s", hipGetErrorString(e));
+            (void)hipDeviceSynchronize();
+        }
+        for (auto& h : held) {
+            if (h.first->ptr) (void)hipFree(h.first->ptr);
+            h.first->ptr = nullptr;
+            h.first->bytes = 0;
         }
     }
     {

@@ -29,11 +29,11 @@ static int thread_no()
     static thread_local const int n = g_threads++;
     return n;
 }
-static void note(const char* what, const void* p, int64_t v = 0, const void* q = nullptr)
+static void note(const char* what, hipStream_t st, const void* p, int64_t v = 0)
 {
     char line[512];
-    snprintf(line, sizeof line, "%s %d %llx %lld %llx\n", what, thread_no(),
-             (unsigned long long)(uintptr_t)p, (long long)v, (unsigned long long)(uintptr_t)q);
+    snprintf(line, sizeof line, "%s %d %llx %llx %lld\n", what, thread_no(),
+             (unsigned long long)(uintptr_t)st, (unsigned long long)(uintptr_t)p, (long long)v);
     std::lock_guard<std::mutex> lk(g_mu);
     g_log += line;
 }
@@ -42,7 +42,7 @@ extern "C" {
 
 void rec_limit(int64_t bytes) { g_limit = bytes; }
 void rec_delay_us(int us) { g_delay_us = us; }
-// Log so far ("what thread pointer value pointer", one event a line), which is then cleared.
+// Log so far ("what thread stream pointer value", one event a line), which is then cleared.
 int64_t rec_take(char* out, int64_t cap)
 {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -85,8 +85,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
     *st = g_call.stream;
     return hipSuccess;
 }
-// k_w* (volumes): value = 0, then the volume and its workspace; kernels over
-// BatchArgs and a Workspace: the merge groups, the workspace.
+// Kernels over a workspace: pointer = the workspace; those over images: value =
+// the merge groups.
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t st)
 {
     if (g_delay_us) usleep((useconds_t)g_delay_us);
@@ -95,16 +95,14 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     size_t n = 0;
     while (k && k[n] && (k[n] == '_' || (k[n] >= 'a' && k[n] <= 'z'))) ++n;
     const std::string what = "launch:" + std::string(k ? k : "?", k ? n : 1);
-    if (name.find("VolArgs") != std::string::npos) {
-        const auto* v = static_cast<const ccl::VolArgs*>(args[0]);
-        const bool ws = name.find("VolWs") != std::string::npos;
-        note(what.c_str(), v->vol, 0, ws ? static_cast<const ccl::VolWs*>(args[1])->bits : nullptr);
+    if (name.find("VolWs") != std::string::npos) {
+        note(what.c_str(), st, static_cast<const ccl::VolWs*>(args[1])->bits);
     } else if (name.find("BatchArgs") != std::string::npos &&
                name.find("Workspace") != std::string::npos) {
-        note(what.c_str(), st, static_cast<const ccl::BatchArgs*>(args[0])->ngroups,
-             static_cast<const ccl::Workspace*>(args[1])->bits);
+        note(what.c_str(), st, static_cast<const ccl::Workspace*>(args[1])->bits,
+             static_cast<const ccl::BatchArgs*>(args[0])->ngroups);
     } else {
-        note(what.c_str(), st);
+        note(what.c_str(), st, nullptr);
     }
     return hipSuccess;
 }
@@ -113,7 +111,7 @@ hipError_t hipMalloc(void** p, size_t bytes)
 {
     *p = nullptr;
     if ((int64_t)bytes > g_limit) {
-        note("refused", nullptr, (int64_t)bytes);
+        note("refused", nullptr, nullptr, (int64_t)bytes);
         return hipErrorOutOfMemory;
     }
     {
@@ -121,12 +119,12 @@ hipError_t hipMalloc(void** p, size_t bytes)
         *p = reinterpret_cast<void*>(g_next);
         g_next += (bytes + 0xffff) & ~size_t(0xffff);
     }
-    note("malloc", *p, (int64_t)bytes);
+    note("malloc", nullptr, *p, (int64_t)bytes);
     return hipSuccess;
 }
 hipError_t hipFree(void* p)
 {
-    note("free", p);
+    note("free", nullptr, p);
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned)
@@ -141,17 +139,17 @@ hipError_t hipHostFree(void* p)
 }
 hipError_t hipStreamSynchronize(hipStream_t st)
 {
-    note("wait", st);
+    note("wait", st, nullptr);
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize()
 {
-    note("wait_device", nullptr);
+    note("wait_device", nullptr, nullptr);
     return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void* dst, const void*, size_t bytes, hipMemcpyKind, hipStream_t)
+hipError_t hipMemcpyAsync(void* dst, const void*, size_t bytes, hipMemcpyKind, hipStream_t st)
 {
-    note("copy", dst, (int64_t)bytes);
+    note("copy", st, dst, (int64_t)bytes);
     return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s)

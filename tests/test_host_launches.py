@@ -22,13 +22,13 @@ lib.ccl_label.argtypes = [p, i32, i32, i64, i32, p, p]
 lib.ccl_label_3d.argtypes = [p, i32, i32, i32, i64, i64, i32, p, p]
 lib.ccl_replay_last.argtypes = [i32, i32, p]
 IN, OUT = 1 << 32, 1 << 36
-Event = collections.namedtuple("Event", "what thread ptr value ptr2")
+Event = collections.namedtuple("Event", "what thread stream ptr value")
 
 def take():
     buf = ctypes.create_string_buffer(1 << 22)
     assert rec.rec_take(buf, len(buf)) < len(buf)
     rows = [l.split() for l in buf.value.decode().splitlines()]
-    return [Event(w, int(t), int(a, 16), int(v), int(b, 16)) for w, t, a, v, b in rows]
+    return [Event(w, int(t), int(s, 16), int(a, 16), int(v)) for w, t, s, a, v in rows]
 
 def image(H, W, conn=8, stream=None, at=0):
     assert lib.ccl_label(IN + at, H, W, W, conn, OUT + 4 * at, stream) == 0
@@ -89,4 +89,69 @@ def test_replays_launch_that_kernel_alone(recorder):
         assert [e.what for e in take()] == ["launch:k_local"] * 3
         lib.ccl_replay_last(2, 0, None)
         assert take() == []
+    """)
+
+
+@pytest.mark.parametrize("call", ["volume(64, 64, 64, 6, st, at)", "volume(64, 64, 64, 26, st, at)",
+                                  "image(1500, 1600, 8, st, at)", "image(300, 300, 4, st, at)"])
+@pytest.mark.parametrize("st", [None, 0x5000])
+def test_calls_of_two_threads_on_one_stream_do_not_mix(recorder, call, st):
+    # the launches of a call share a workspace with those of every other call
+    # on the stream, so no other call's may come between them
+    recorder(f"""
+        st = {st}
+        def calls(at):
+            for _ in range(12):
+                {call}
+        calls(0)
+        per_call = len([e for e in take() if e.what.startswith("launch")]) // 12
+        assert per_call >= 3
+        rec.rec_delay_us(300)
+        threads = [threading.Thread(target=calls, args=(t << 20,)) for t in (1, 2, 3)]
+        for t in threads: t.start()
+        for t in threads: t.join()
+        log = [e for e in take() if e.what.startswith("launch")]
+        assert len(log) == 3 * 12 * per_call
+        for i in range(0, len(log), per_call):
+            assert len({{e.thread for e in log[i:i + per_call]}}) == 1, log[i:i + per_call]
+        assert len({{e.thread for e in log}}) == 3
+    """)
+
+
+@pytest.mark.parametrize("conn", [6, 26])
+def test_a_workspace_is_in_nobodys_use_when_it_is_freed(recorder, conn):
+    # threads label growing volumes on one stream and on others while another
+    # one gives the workspaces back: a launch uses a buffer that is there, and a
+    # buffer goes after a wait that follows its last launch
+    recorder(f"""
+        rec.rec_delay_us(100)
+        def calls(st, at):
+            for k in range(1, 13):
+                volume(16 * k, 32, 64, {conn}, st, at)
+                image(70 * k, 300, 8, st, at)
+        def release():
+            for _ in range(20):
+                assert lib.ccl_release_workspace(0) == 0
+        threads = [threading.Thread(target=calls, args=(st, t << 24)) for t, st in
+                   enumerate((0x5000, 0x5000, 0x6000))] + [threading.Thread(target=release)]
+        for t in threads: t.start()
+        for t in threads: t.join()
+        lib.ccl_release_workspace(0)
+        size, freed = {{}}, 0
+        dirty = set()  # (stream, workspace) of launches not waited for
+        for e in take():
+            if e.what == "malloc":
+                size[e.ptr] = e.value
+            elif e.what.startswith("launch"):
+                assert any(b <= e.ptr < b + n for b, n in size.items()), e
+                dirty.add((e.stream, e.ptr))
+            elif e.what == "wait":
+                dirty = {{d for d in dirty if d[0] != e.stream}}
+            elif e.what == "wait_device":
+                dirty.clear()
+            elif e.what == "free":
+                n = size.pop(e.ptr)
+                assert not any(e.ptr <= at < e.ptr + n for _, at in dirty), e
+                freed += 1
+        assert freed > 3 and not size
     """)
