@@ -33,7 +33,10 @@
  * The library owns a per-(device, stream) workspace cache that grows on
  * demand (hipMalloc); concurrent calls on DIFFERENT streams use different
  * workspaces and may overlap freely.  Calls on the same stream are ordered
- * by the stream; several threads may make them.
+ * by the stream; several threads may make them.  hipStreamPerThread is one
+ * handle for a stream of each thread, and one workspace: image calls on it
+ * from several threads have to be ordered by the caller (volumes need none
+ * there).
  */
 #ifndef CCL_H
 #define CCL_H
@@ -191,8 +194,8 @@ int ccl_label_stats(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  * written once: a cached buffer of the stream's apart from that of image calls
  * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks).
  * Smaller volumes, thin ones whose whole bricks would take over 150 MB, calls
- * on a stream that is being captured and calls whose workspace cannot be had
- * need none.  The labels are the same.
+ * on a stream that is being captured or on hipStreamPerThread and calls whose
+ * workspace cannot be had need none.  The labels are the same.
  *   vol           device, uint8, D slices of H rows; row y of slice z starts
  *                 at vol + z * slice_pitch_bytes + y * pitch_bytes;
  *                 caller-owned, only read.

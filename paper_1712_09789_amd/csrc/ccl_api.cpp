@@ -551,6 +551,8 @@ static int label_one(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, in
 //    54, 2 x 1000 x 1000 37 / 57 and 31 / 36; 512^3 blobs at 26: 739 and 214;
 //  * thin volumes whose workspace would be large (over 150 MB with bricks less
 //    than a third full; at a full 64 x 16 x 16 it is 2.3 bytes per voxel);
+//  * hipStreamPerThread, one handle for a stream of each thread, which the
+//    cache would give one buffer;
 //  * a workspace that cannot be had, and calls on a stream that is being
 //    captured, where nothing may be allocated and the graph may outlive this
 //    stream's workspace.
@@ -558,7 +560,7 @@ static bool volume_workspace(const VolArgs& v, int conn, hipStream_t st, VolWs* 
 {
     const int64_t nb = (int64_t)v.wnbx * v.wnby * v.wnbz;
     const int64_t n = (int64_t)v.D * v.H * v.W;
-    if ((int64_t)v.D * v.H < 32 ||
+    if (st == hipStreamPerThread || (int64_t)v.D * v.H < 32 ||
         (nb > 4096 && nb * (VOL_WS_W * VOL_WS_H * VOL_WS_D) > 3 * n) ||
         nb * vol_ws_nodes(conn) > (int64_t)INT32_MAX)
         return false;

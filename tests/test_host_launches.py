@@ -155,3 +155,35 @@ def test_a_workspace_is_in_nobodys_use_when_it_is_freed(recorder, conn):
                 freed += 1
         assert freed > 3 and not size
     """)
+
+
+@pytest.mark.parametrize("conn", [6, 26])
+def test_volumes_on_the_per_thread_stream_share_nothing(recorder, conn):
+    # hipStreamPerThread is one handle for a stream of each thread
+    recorder(f"""
+        volume(64, 64, 64, {conn}, 2)
+        assert [e.what for e in take()] == ["launch:k_vlocal", "launch:k_vmerge", "launch:k_vfinal"]
+    """)
+
+
+@pytest.mark.parametrize("conn", [6, 26])
+def test_volumes_without_a_workspace_are_labelled_in_place(recorder, conn):
+    # no memory for a first workspace, then for a larger one; the call succeeds,
+    # and goes back to a workspace once it can be had
+    recorder(f"""
+        here = ["launch:k_vlocal", "launch:k_vmerge", "launch:k_vfinal"]
+        there = ["launch:k_wlocal", "launch:k_wmerge", "launch:k_wfinal"]
+        launches = lambda: [e.what for e in take() if e.what.startswith("launch")]
+        rec.rec_limit(1000)
+        volume(64, 64, 64, {conn})
+        assert launches() == here
+        rec.rec_limit(1 << 40)
+        volume(64, 64, 64, {conn})
+        assert launches() == there
+        rec.rec_limit(1000)
+        volume(200, 300, 300, {conn})
+        assert launches() == here
+        rec.rec_limit(1 << 40)
+        volume(200, 300, 300, {conn})
+        assert launches() == there
+    """)
