@@ -192,7 +192,9 @@ int ccl_label_stats(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  * label is rewritten to its root.  Volumes of 32 rows or more are labelled
  * through a workspace, in bricks of 64 x 16 x 16 voxels, and each label is
  * written once: a cached buffer of the stream's apart from that of image calls
- * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks).
+ * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks; kept
+ * with a quarter more until ccl_release_workspace, which
+ * ccl_volume_workspace_cached reports).
  * Smaller volumes, thin ones whose whole bricks would take over 150 MB, calls
  * on a stream that is being captured or on hipStreamPerThread and calls whose
  * workspace cannot be had need none.  The labels are the same.
@@ -299,6 +301,8 @@ int64_t ccl_workspace_bytes(int32_t H, int32_t W);
    that stream and is kept until ccl_release_workspace.  For callers that
    account device memory (a serving loop's admission). */
 int64_t ccl_workspace_cached(void* stream);
+/* The same of the buffer kept for volumes (ccl_label_3d). */
+int64_t ccl_volume_workspace_cached(void* stream);
 
 /* Thread-local message describing the last non-OK status ("" if none). */
 const char* ccl_last_error(void);

@@ -74,6 +74,8 @@ def _load() -> ctypes.CDLL:
     lib.ccl_workspace_bytes.argtypes = [i32, i32]
     lib.ccl_workspace_cached.restype = i64
     lib.ccl_workspace_cached.argtypes = [vp]
+    lib.ccl_volume_workspace_cached.restype = i64
+    lib.ccl_volume_workspace_cached.argtypes = [vp]
     lib.ccl_last_error.restype = ctypes.c_char_p
     lib.ccl_release_workspace.restype = ctypes.c_int
     lib.ccl_release_workspace.argtypes = [i32]
@@ -403,8 +405,15 @@ def workspace_bytes(H: int, W: int) -> int:
 
 
 def workspace_cached(stream=None) -> int:
-    """Bytes of the library workspace kept for `stream` (current device)."""
+    """Bytes of the library workspace kept for image calls on `stream`
+    (current device)."""
     return int(_lib.ccl_workspace_cached(_stream_handle(stream)))
+
+
+def volume_workspace_cached(stream=None) -> int:
+    """Bytes of the library workspace kept for label_3d on `stream` (current
+    device)."""
+    return int(_lib.ccl_volume_workspace_cached(_stream_handle(stream)))
 
 
 def release_workspace(device: int = 0) -> None:

@@ -1028,14 +1028,16 @@ int64_t ccl_workspace_bytes(int32_t H, int32_t W)
     return most;
 }
 
-int64_t ccl_workspace_cached(void* stream)
+static int64_t workspace_cached(void* stream, WsKind kind)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    const auto it = g_ws.find({dev, static_cast<hipStream_t>(stream), WS_IMAGES});
+    const auto it = g_ws.find({dev, static_cast<hipStream_t>(stream), kind});
     return it == g_ws.end() ? 0 : it->second.bytes.load();
 }
+int64_t ccl_workspace_cached(void* stream) { return workspace_cached(stream, WS_IMAGES); }
+int64_t ccl_volume_workspace_cached(void* stream) { return workspace_cached(stream, WS_VOLUMES); }
 
 const char* ccl_last_error(void) { return g_err.c_str(); }
 

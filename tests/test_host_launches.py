@@ -187,3 +187,26 @@ def test_volumes_without_a_workspace_are_labelled_in_place(recorder, conn):
         volume(200, 300, 300, {conn})
         assert launches() == there
     """)
+
+
+@pytest.mark.parametrize("conn,per_brick", [(6, 37460), (26, 14036)])
+def test_kept_volume_workspaces_are_reported(recorder, conn, per_brick):
+    recorder(f"""
+        for f in (lib.ccl_workspace_cached, lib.ccl_volume_workspace_cached):
+            f.argtypes, f.restype = [p], i64
+        held = lambda st=None: (lib.ccl_workspace_cached(st), lib.ccl_volume_workspace_cached(st))
+        assert held() == (0, 0)
+        image(300, 300)
+        images = held()[0]
+        assert images > 0 and held()[1] == 0
+        take()
+        volume(33, 40, 70, {conn})  # 3 x 3 x 2 bricks
+        allocated = sum(e.value for e in take() if e.what == "malloc")
+        assert held() == (images, allocated) and held(0x5000) == (0, 0)
+        need = 18 * {per_brick}
+        assert 1.25 * need <= allocated <= 1.25 * (need + 5 * 256)
+        volume(16, 16, 64, {conn})
+        assert held() == (images, allocated)
+        lib.ccl_release_workspace(0)
+        assert held() == (0, 0)
+    """)
