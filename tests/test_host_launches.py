@@ -210,3 +210,16 @@ def test_kept_volume_workspaces_are_reported(recorder, conn, per_brick):
         lib.ccl_release_workspace(0)
         assert held() == (0, 0)
     """)
+
+
+@pytest.mark.parametrize("conn", [6, 26])
+def test_rules_of_the_volume_paths(recorder, conn):
+    # 32 rows; more than 4096 bricks less than a third full
+    recorder(f"""
+        for shape, path in (((1, 31, 500), "v"), ((1, 32, 500), "w"), ((31, 1, 500), "v"),
+                            ((4, 8, 500), "w"), ((2, 16, 64 * 4096), "w"),
+                            ((2, 16, 64 * 4096 + 1), "v"), ((6, 16, 64 * 4096 + 1), "w")):
+            volume(*shape, {conn})
+            got = [e.what for e in take() if e.what.startswith("launch")]
+            assert got and all(k.startswith("launch:k_" + path) for k in got), (shape, got)
+    """)
