@@ -274,7 +274,11 @@ __device__ __forceinline__ void st_labels4(int32_t* p, int32_t a, int32_t b, int
     v.y = (uint32_t)b;
     v.z = (uint32_t)c;
     v.w = (uint32_t)d;
-    st_global(reinterpret_cast<v4u32u*>(p), v);
+#if defined(__HIP_DEVICE_COMPILE__)
+    *(__attribute__((address_space(1))) v4u32u*)p = v;
+#else
+    *reinterpret_cast<v4u32u*>(p) = v;  // host pass: never executed
+#endif
 }
 // The same around the caches, for rows that are whole 128-byte lines (8192^2
 // Bernoulli 0.6: k_final 74 -> 59 us; on rows of other widths the half-written
