@@ -195,9 +195,9 @@ int ccl_label_stats(const uint8_t* img, int32_t H, int32_t W, int64_t pitch_byte
  * (2.3 bytes per voxel at 6-connectivity, 0.9 at 26, in whole bricks; kept
  * with a quarter more until ccl_release_workspace, which
  * ccl_volume_workspace_cached reports).
- * Smaller volumes, thin ones whose whole bricks would take over 150 MB, calls
- * on a stream that is being captured or on hipStreamPerThread and calls whose
- * workspace cannot be had need none.  The labels are the same.
+ * Smaller volumes, thin ones of more than 4096 bricks less than a third full,
+ * calls on a stream that is being captured or on hipStreamPerThread and calls
+ * whose workspace cannot be had need none.  The labels are the same.
  *   vol           device, uint8, D slices of H rows; row y of slice z starts
  *                 at vol + z * slice_pitch_bytes + y * pitch_bytes;
  *                 caller-owned, only read.

@@ -334,8 +334,9 @@ static Choice choose(bool batch, int64_t px, int conn, int forced_rows)
 // than the launch.  640 x 480 (40 tiles of 128 rows) and 2048^2 (512) blobs,
 // Bernoulli 0.41 and serpentine at 8-connectivity: 18.3, 24.3 and 21.7 us
 // against 22.9, 27.8 and 22.2; 26.6, 37.6, 34.6 against 29.1, 37.1, 29.5;
-// 3000^2 (1128): 37.6, 54.9, 56.8 against 37.9, 53.2, 44.1.  Images of one
-// group keep k_block, which is all their merge and leaves their forest flat.
+// 3000^2 (1128): 37.6, 54.9, 56.8 against 37.9, 53.2, 44.1.  At the line itself
+// one long chain already loses and regions still gain, noise is level.  Images of
+// one group keep k_block, which is all their merge and leaves their forest flat.
 constexpr int64_t DIRECT_TILES = 512;
 
 // Launches whose label maps exceed this write them around the caches (images
@@ -544,13 +545,15 @@ static int label_one(const uint8_t* img, int32_t H, int32_t W, int64_t pitch, in
 // none:
 //  * fewer than 32 rows: a brick here has 256 rows and its fixed cost shows
 //    (1 x 1 x 5000 voxels: 13.5 us in place, 16.7 here; 2 x 8 x 64: 9-22 and
-//    11).  From there on this path wins at every size; in place and here, us at
-//    6 / 26 neighbours on Bernoulli 0.35 / 0.2: 7 x 7 x 50 11.8 / 16.6 and 11.7
-//    / 14.7, 1 x 512 x 512 20 / 25 and 19 / 22, 33 x 40 x 43 43 / 44 and 31 / 35,
-//    64^3 45 / 46 and 37 / 47, 128^3 57 / 58 and 41 / 50, 150^3 78 / 70 and 47 /
-//    54, 2 x 1000 x 1000 37 / 57 and 31 / 36; 512^3 blobs at 26: 739 and 214;
-//  * thin volumes whose workspace would be large (over 150 MB with bricks less
-//    than a third full; at a full 64 x 16 x 16 it is 2.3 bytes per voxel);
+//    11).  From there on this path is the faster, or within 1 us (64^3 at 26);
+//    in place and here, us at 6 / 26 neighbours on Bernoulli 0.35 / 0.2: 7 x 7 x
+//    50 11.8 / 16.6 and 11.7 / 14.7, 1 x 512 x 512 20 / 25 and 19 / 22, 33 x 40 x
+//    43 43 / 44 and 31 / 35, 64^3 45 / 46 and 37 / 47, 128^3 57 / 58 and 41 / 50,
+//    150^3 78 / 70 and 47 / 54, 2 x 1000 x 1000 37 / 57 and 31 / 36; 512^3 blobs
+//    at 26: 739 and 214;
+//  * thin volumes whose workspace would be large beside them (more than 4096
+//    bricks, 153 MB at 6-connectivity and 57 at 26, less than a third full; in
+//    full bricks it is 2.3 and 0.9 bytes per voxel);
 //  * hipStreamPerThread, one handle for a stream of each thread, which the
 //    cache would give one buffer;
 //  * a workspace that cannot be had, and calls on a stream that is being
@@ -599,7 +602,7 @@ static Choice builtin_choice() { return Choice{&r64::ops, GridChoice{}}; }
 // not device memory: its device address is looked up once per device
 // (hipGetSymbolAddress, with that device current) and only that address is
 // ever passed to kernels.  Nothing in the workspace needs to start at zero:
-// the local step writes every entry the later kernels read.
+// each kernel reads only entries that an earlier one of the same call wrote.
 
 constexpr int64_t NOALLOC_SCRATCH_BYTES = int64_t(32) << 20;
 static __device__ __align__(256) uint8_t scratch[NOALLOC_SCRATCH_BYTES];

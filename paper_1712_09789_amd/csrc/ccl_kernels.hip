@@ -159,7 +159,10 @@ __device__ uint32_t pfind(uint32_t* P, uint32_t x)
 }
 
 // Counting versions for the ablation study: `it` counts steps of the find
-// loops (the paper's iterations), `at` the atomic merge attempts.
+// loops (the paper's iterations), `at` the atomic merge attempts.  The union is
+// the paper's (find both roots, then merge), not the joint climb of punion
+// below, whose steps are finds and merges in one: all four variants count the
+// same two things, and their counts are not those of k_local.
 __device__ uint32_t pfind_count(uint32_t* P, uint32_t x, uint32_t& it)
 {
     uint32_t v = lds_ld(P + x);
@@ -263,9 +266,9 @@ __device__ __forceinline__ void st_global16(void* p, int32_t a, int32_t b, int32
 
 // The same at any multiple of four bytes: label rows of odd widths start
 // anywhere, and a store that straddles two cache lines costs less than four
-// stores (256 images of random widths: k_final 121 us with dword stores of
-// sixteen consecutive labels, 117 with these; 201 x 301 x 333 volume: k_wfinal
-// 35 with a row per wavefront store, 28).
+// stores (256 images of random widths: k_final 151 us with dword stores, 130
+// with these; 1077 x 1913: 7.9 and 6.5; 201 x 301 x 333 volume: k_wfinal 37 and
+// 23).
 typedef uint32_t v4u32u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void st_labels4(int32_t* p, int32_t a, int32_t b, int32_t c, int32_t d)
 {
@@ -282,7 +285,7 @@ __device__ __forceinline__ void st_labels4(int32_t* p, int32_t a, int32_t b, int
 }
 // The same around the caches, for rows that are whole 128-byte lines (8192^2
 // Bernoulli 0.6: k_final 74 -> 59 us; on rows of other widths the half-written
-// lines cost more than the cache: 256 mixed images 117 -> 184).
+// lines cost more than the cache: 256 mixed images 129 -> 184).
 __device__ __forceinline__ void st_labels4_nt(int32_t* p, int32_t a, int32_t b, int32_t c,
                                               int32_t d)
 {
@@ -593,8 +596,8 @@ __global__ __launch_bounds__(256) void k_index(BatchArgs b)
 // place.  A block is loaded only when it holds a byte of the segment, so it
 // lies in the same memory page as image bytes (blocks never cross a page);
 // its other bytes are masked off, as are pixels past the image edge.  The
-// raw blocks are returned so that the loads of the next tile can be in
-// flight while the current one is labelled.
+// raw blocks are returned so that all loads of a thread are in flight before
+// the first is used.
 struct Chunk {
     uint4 lo, hi;   // the aligned blocks
     uint32_t off;   // byte of the segment's first pixel in lo
@@ -2128,7 +2131,8 @@ static_assert(VB_ROWS * 4 == VNT && VB_ROWS == 64, "one 16-voxel segment per thr
 static_assert(VB_ROWS * VB_W <= 0x8000 && VMAXR <= 0x10000, "16-bit keys and run ids");
 
 // Entry of a node during the merge: the first two hops of a find use plain
-// loads, later ones coherent loads (as g_hop for the 2-D forest).
+// loads, later ones coherent loads (a stale entry still names an ancestor, and
+// a stale "root" is caught by the link's atomic min, as at g_hop).
 __device__ __forceinline__ uint32_t vl_hop(const int32_t* p, int step)
 {
     return (uint32_t)(step < 2 ? ld_global(p)
@@ -2138,9 +2142,13 @@ __device__ __forceinline__ uint32_t vl_hop(const int32_t* p, int step)
 
 // Root of r, given its parent p and grandparent pp (p not a root, pp != p):
 // halves the path on the way, with plain stores of ancestors into entries
-// read as non-roots (safe for the reasons given at g_find_from).  Entries
-// always name smaller positions, so a chase ends at a root; the bound check
-// only keeps a corrupted entry from reading outside the map.
+// read as non-roots.  A root is never stored to, and a node that has a parent
+// never becomes a root again.  A store may replace a parent that another
+// thread's atomic min set meanwhile, after a stale read of the node as a root:
+// that thread goes on uniting the parent it got back with the one it set, so
+// all parents a node has had end in one component and no union is lost.
+// Entries always name smaller positions, so a chase ends at a root; the bound
+// check only keeps a corrupted entry from reading outside the map.
 __device__ uint32_t v_find_on(int32_t* lab, uint32_t r, uint32_t p, uint32_t pp, uint32_t n)
 {
     for (int step = 2;; step += 2) {
